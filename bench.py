@@ -315,18 +315,43 @@ def rocsparse_compare(g, Fs, Xs, Ys, d_rowptr, d_colidx, d_vals, stream, reps):
     return out
 
 
+# Dense matrix peaks: fp32, and bf16 over the six part products that stand for
+# one fp32 product in k_linear_split and k_linear_ksplit.
 MFMA_FP32_PEAK_TFLOPS = 157.3
+MFMA_SPLIT_PEAK_TFLOPS = 2500.0 / 6
 
 
 def linear_kernel_name(fin, fout):
-    """Instantiation agcn_linear picks for compact, 16-byte aligned float32 X and
-    W (AGCN_LINEAR_RW=0 forces the tiled kernel)."""
+    """Name by which records made with the fp32 linear kernels (k_linear_rw with
+    W resident, the tiled k_linear) list a shape; linear_kernel names today's."""
     vec = fin % 4 == 0 and fout % 4 == 0
-    if vec and 1 <= fin <= 128 and fout <= 128 and os.environ.get("AGCN_LINEAR_RW", "1") != "0":
+    if vec and 1 <= fin <= 128 and fout <= 128:
         nb = 2 if fout <= 32 else 4 if fout <= 64 else 8
         ks = 2 if fin <= 32 else 4 if fin <= 64 else 8
         return f"k_linear_rw<{nb}, {ks}>"
     return f"k_linear<{32 if fout <= 32 else 64 if fout <= 64 else 128}, {'true' if vec else 'false'}>"
+
+
+def linear_kernel(n, fin, fout):
+    """Kernel agcn_linear picks for compact, 16-byte aligned float32 matrices."""
+    cdiv = lambda a, b: -(-a // b)
+    if fin % 4 == 0 and fout % 4 == 0 and 1 <= fin < 32:
+        return f"k_linear_rw<{2 if fout <= 32 else 4 if fout <= 64 else 8}>"
+    if fin > 32 and cdiv(n, 16) * cdiv(fout, 64) <= 1024:
+        return f"k_linear_ksplit<{1 if fout <= 16 else 2 if fout <= 32 else 4}, {8 if fin > 256 else 4}>"
+    if fout <= 16:
+        return "k_linear_split<1, 1, 4>"
+    if fout <= 32:
+        return "k_linear_split<2, 2, 4>"
+    if cdiv(n, 128) * cdiv(fout, 64) < 512 and fin <= 256:
+        return "k_linear_split<1, 4, 4>"
+    if fout <= 48:
+        return "k_linear_split<2, 3, 4>"
+    if fout <= 64 or fin <= 64:
+        return "k_linear_split<2, 4, 4>"
+    if fin >= 256 and (fout - 1) % 256 >= 128:
+        return "k_linear_split<2, 16, 8>"
+    return "k_linear_split<1, 8, 8>"
 
 
 def bench_layer(args):
@@ -395,7 +420,13 @@ def bench_layer(args):
     fl_lin = 2.0 * g.n_cols * fin * fout
     fl_agg = 2.0 * g.nnz * fout
     ach = fl_lin / (lin_ms * 1e-3) / 1e12
-    kname = linear_kernel_name(fin, fout)
+    kname = linear_kernel(g.n_cols, fin, fout)
+    peak = MFMA_FP32_PEAK_TFLOPS if "_rw" in kname else MFMA_SPLIT_PEAK_TFLOPS
+    lin_bytes = int(4 * g.n_cols * (fin + fout) + 4 * fin * fout)
+    if lin_bytes / (HBM_PEAK_GBPS * 1e9) > fl_lin / (peak * 1e12):
+        bound, unit, ach, peak = "hbm", "GB/s", lin_bytes / (lin_ms * 1e-3) / 1e9, HBM_PEAK_GBPS
+    else:
+        bound, unit = "mfma", "TFLOP/s"
     out = {
         "metric": "GCNConv layer forward GFLOP/s (2·N·fin·fout + 2·nnz·fout)",
         "value": round((fl_lin + fl_agg) / (ms_step * 1e-3) / 1e9, 3), "unit": "GFLOP/s",
@@ -406,10 +437,9 @@ def bench_layer(args):
                    "activation": "relu", "parallelism": "single GPU"},
         "plan_ms_once": round(plan_ms, 4), "linear_ms": round(lin_ms, 5),
         "aggregation_ms": round(agg_ms, 5),
-        "roofline": {"bound": "mfma", "achieved": round(ach, 2), "peak": MFMA_FP32_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": round(ach / MFMA_FP32_PEAK_TFLOPS, 4),
-                     "traffic": None, "kernel": kname,
-                     "hbm_bytes_alg": int(4 * g.n_cols * (fin + fout) + 4 * fin * fout)},
+        "roofline": {"bound": bound, "achieved": round(ach, 2), "peak": round(peak, 1),
+                     "unit": unit, "frac": round(ach / peak, 4),
+                     "traffic": None, "kernel": kname, "hbm_bytes_alg": lin_bytes},
     }
     print(json.dumps(out), flush=True)
 

@@ -254,19 +254,22 @@ int agcn_spmm_noalloc(agcn_plan_t plan, int32_t F, const float* d_X, int64_t ldx
                       int64_t ldy, void* stream, int32_t epilogue);
 
 /* H = X W, the linear transformation of a GCNConv layer (Sec. II-A), on the
- * fp32 matrix cores. Asynchronous on `stream`; no plan needed.
+ * matrix cores. Asynchronous on `stream`; no plan needed.
  *
  * d_X: n rows of fin floats, row stride ldx >= fin; d_W: fin rows of fout
  * floats, stride ldw >= fout; d_H: n rows of fout floats, stride ldh >= fout.
  * All row-major, device memory owned by the caller; H must not overlap X or
- * W. fin = 0 gives H = 0. fp32 products and sums (matrix-core accumulation,
- * fin terms per element). Kernel choice: with fin at most 128, fin, fout,
- * ldx, ldw and ldh multiples of 4, X, W and H 16-byte aligned and X and H
- * each under 4 GiB, W stays resident on chip while X streams past (once per
- * 128 output columns); otherwise a tiled kernel runs (128-bit loads when fin, fout, ldx and ldw are
- * multiples of 4 and X, W are 16-byte aligned, else 32-bit loads with the
- * same results). The two kernels add the fin products in different orders,
- * so their results may differ in the last bits; each is deterministic.
+ * W. fin = 0 gives H = 0. fp32 accuracy and range: X and W enter the bf16
+ * matrix cores as three bf16 parts each (24 bits), six part products added in
+ * fp32; elements that are not finite are computed again with an fp32 sum, so
+ * infinities and NaN are those of the fp32 product. Any alignment and stride
+ * takes the same kernels. For fin < 32 with fin, fout, ldx, ldw and ldh
+ * multiples of 4, X, W and H 16-byte aligned and X and H each under 4 GiB,
+ * the fp32 matrix instruction runs instead with W resident on chip. For few
+ * rows the fin terms are summed in several runs that are then added. The
+ * kernels add the fin products in different orders, so results may differ in
+ * the last bits between shapes; each is deterministic, and a row's result
+ * does not depend on its position.
  * Errors: INVALID_ARGUMENT (negative sizes, ld too small, NULL pointers with
  * non-empty extents, overlap), UNSUPPORTED (more than 2^32 - 1 tiles), HIP. */
 int agcn_linear(int64_t n, int32_t fin, int32_t fout, const float* d_X, int64_t ldx,

@@ -1,0 +1,92 @@
+"""agcn_linear's kernels at the sizes where they can go wrong: chunks of 32 k
+(edges and remainders), tiles of 16 to 256 columns and 16 to 128 rows, the
+k split for few rows, unaligned data, and values outside bf16's range.
+
+Tolerance per element: (fin + 12) u |X||W| + fin 2^-133 (u = 2^-24). The parts'
+products are exact; an element sees 6 ceil(fin / 32) matrix instructions, each
+off by at most 2 u of the largest partial sum (at most |X||W|), at most
+fin + 10 u in all for every fin here, and the products left out are below
+2 u; a part below bf16's smallest number is lost, at most 2^-134 each.
+"""
+import numpy as np
+import pytest
+
+import graphgen
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2308_11825_amd as agcn  # noqa: E402
+
+from gpu_helpers import DEV, _dev  # noqa: E402
+
+U = 2.0 ** -24
+
+
+def _check(X, W, H):
+    fin = W.shape[0]
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = X.astype(np.float64) @ W.astype(np.float64)
+        S = np.abs(X.astype(np.float64)) @ np.abs(W.astype(np.float64))
+        ref32 = ref.astype(np.float32)
+        finite = np.isfinite(ref32)
+        assert np.array_equal(np.isnan(H), np.isnan(ref32))
+        assert np.array_equal(H[~finite & ~np.isnan(ref32)], ref32[~finite & ~np.isnan(ref32)])
+        err = np.abs(H.astype(np.float64) - ref)[finite]
+    tol = ((fin + 12) * U * S + fin * 2.0 ** -133)[finite]
+    assert (err <= tol).all(), (float((err / tol).max()), X.shape, W.shape)
+
+
+def _xw(n, fin, fout):
+    rng = np.random.default_rng(n * 7 + fin * 3 + fout)
+    return rng.standard_normal((n, fin)).astype(np.float32), graphgen.weights(fin, fout, seed=n + fout)
+
+
+# rows: one, a remainder of every row tile, past the k split's line; fin: chunk
+# edges; fout: edges of every column tile (16, 32, 48, 64, 128, 256)
+@pytest.mark.parametrize("n,fin,fout", [
+    (1, 1, 1), (15, 31, 15), (17, 33, 17), (16, 64, 16), (129, 65, 33), (63, 256, 48), (65, 257, 49),
+    (3000, 1000, 16), (1000, 300, 130), (3001, 95, 64), (20000, 36, 65), (40001, 32, 47),
+    (40003, 29, 48), (66000, 64, 64), (70000, 66, 128), (70001, 100, 129), (40000, 256, 255),
+    (33000, 259, 256), (70000, 31, 3), (40007, 127, 1), (50000, 12, 132), (100003, 28, 32)])
+def test_linear_tile_edges(n, fin, fout):
+    X, W = _xw(n, fin, fout)
+    print(f"[linear split] n={n} fin={fin} fout={fout}", flush=True)
+    _check(X, W, agcn.linear(_dev(X), _dev(W)).cpu().numpy())
+
+
+@pytest.mark.parametrize("n,fin,fout", [(2049, 70, 41), (70000, 70, 41), (40000, 300, 200)])
+def test_linear_unaligned_rows_and_padding(n, fin, fout):
+    """Odd offsets and strides on every matrix; infinities in the padding of X
+    and W are never used, the padding of H never written."""
+    X, W = _xw(n, fin, fout)
+    xb = torch.full((n * (fin + 3) + 1,), float("inf"), device=DEV)
+    Xd = xb[1:].view(n, fin + 3)[:, :fin]
+    Xd.copy_(_dev(X))
+    wb = torch.full((fin * (fout + 1) + 3,), float("nan"), device=DEV)
+    Wd = wb[3:].view(fin, fout + 1)[:, :fout]
+    Wd.copy_(_dev(W))
+    hb = torch.full((n * (fout + 5) + 2,), 4.0, device=DEV)
+    Hp = hb[2:].view(n, fout + 5)
+    agcn.linear(Xd, Wd, out=Hp[:, :fout])
+    _check(X, W, Hp[:, :fout].cpu().numpy())
+    assert torch.all(Hp[:, fout:] == 4.0) and torch.all(hb[:2] == 4.0)
+
+
+@pytest.mark.parametrize("n", [500, 40000])     # the k split, the tiles
+def test_linear_infinities_nan_and_extreme_values(n):
+    """Elements that meet an infinity or a NaN, or values that round past
+    bf16's largest, come out as in a float32 product; their neighbours are not
+    touched. Zero times infinity is NaN, an infinity times a weight infinite."""
+    X, W = _xw(n, 70, 40)
+    X[3, 5], X[4, 69], X[5, 0], X[6, 33] = np.inf, -np.inf, np.nan, 3.4e38
+    X[7], X[8], X[9] = 0.0, 1e-39, 1e-42
+    X[n - 1, 1] = np.inf
+    W[5, 3], W[69, 7] = 0.0, -2.0
+    W[10, 11] = np.inf
+    W[33, :] = 0.25
+    H = agcn.linear(_dev(X), _dev(W)).cpu().numpy()
+    _check(X, W, H)
+    assert np.isnan(H[3, 3]) and np.isinf(H[4, 7]) and np.isfinite(H[6, :11]).all()
+    clean = agcn.linear(_dev(X[20:21]), _dev(W)).cpu().numpy()
+    assert np.isfinite(np.delete(H[20], 11)).all() and np.isfinite(np.delete(clean[0], 11)).all()
