@@ -189,9 +189,11 @@ int agcn_spmm_workspace_size(agcn_plan_t plan, int32_t F, size_t* bytes);
  * rows, stride ldy >= F. Every Y row is written exactly once (empty rows get
  * zeros), so Y needs no clearing. X and Y must not overlap. d_ws: at least
  * agcn_spmm_workspace_size(plan, F) bytes, may be NULL when that is 0.
- * The 128-bit path runs when F, ldx and ldy are multiples of 4 and X, Y, ws
- * are 16-byte aligned; otherwise a 32-bit path runs (same results up to
- * float rounding order, both deterministic).
+ * X, Y and ws need 4-byte alignment only, and any strides: from F = 4 up every
+ * layout takes 128-bit accesses (the ablation plans: when F, ldx and ldy are
+ * multiples of 4 and X, Y, ws 16-byte aligned, else 32-bit ones). Rows of X
+ * that start on 128-byte lines are the fastest. "The 128-bit path" below:
+ * those multiples and alignments.
  * Result: bitwise reproducible run to run; no atomics. The hub rows of a plan
  * with hub-row windows are summed window by window at F >= 64 on the
  * 128-bit path and by hub chunks otherwise (same sums, another rounding

@@ -1,7 +1,8 @@
 // Execute: Y = A X over the block-level partition (Sec. III-C, III-D).
 //
 // k_spmm: one workgroup per (metadata entry, column slice). A column slice is
-// 32 floats -- one 128-byte line of an X row -- unless F is smaller. The grid
+// 32 floats -- one 128-byte line of an X row -- unless F is smaller or the rows
+// of X do not start on lines (slice_width). The grid
 // is (entries, slices) and workgroups are dispatched x-fastest, so the whole
 // GPU sweeps the entries for slice 0, then slice 1, ...: at any moment the
 // L2 of every XCD holds only 128-byte pieces of X rows, which lets it keep
@@ -67,11 +68,36 @@ struct VecOf;
 template <>
 struct VecOf<4> {
   using T = f4;
+  // In memory: 16-byte accesses that need 4-byte alignment only.
+  typedef float M __attribute__((ext_vector_type(4), aligned(4)));
 };
 template <>
 struct VecOf<1> {
   using T = float;
+  using M = float;
 };
+
+// First column of lane l in a slice of `cols` columns. Where cols is no
+// multiple of VW the last lane starts early and shares columns with the lane
+// before it: both compute and write the same values.
+template <int VW>
+__device__ inline int lane_col(int l, int cols) {
+  return VW == 4 ? min(4 * l, cols - 4) : l;
+}
+
+template <int VW>
+__device__ inline typename VecOf<VW>::T load_v(const float* p) {
+  return *reinterpret_cast<const typename VecOf<VW>::M*>(p);
+}
+template <int VW>
+__device__ inline void store_v(float* p, typename VecOf<VW>::T v) {
+  *reinterpret_cast<typename VecOf<VW>::M*>(p) = v;
+}
+template <int VW>
+__device__ inline void store_nt(float* p, typename VecOf<VW>::T v) {
+  const typename VecOf<VW>::M m = v;
+  __builtin_nontemporal_store(m, reinterpret_cast<typename VecOf<VW>::M*>(p));
+}
 
 constexpr int kDefaultSliceCols = 32;  // one 128-byte line per X row per pass
 // Slice width of column-ordered hub chunks of long hub rows (two lines).
@@ -105,14 +131,15 @@ __device__ inline f4 act_v(f4 v, int32_t act) {
   return act ? f4{act_v(v.x, 1), act_v(v.y, 1), act_v(v.z, 1), act_v(v.w, 1)} : v;
 }
 
-// acc = sum over j in [s0, s0 + len) of val[j] * X[col[j], lane], in order.
+// acc = sum over j in [s0, s0 + len) of val[j] * X[col[j], lane], in order (Xl:
+// X at the lane's first column).
 // Groups of kGatherUnroll loads are issued before the first is consumed; the
 // tail of a group is predicated, so short slices still overlap their loads.
 template <int VW>
 __device__ inline typename VecOf<VW>::T gather_row(const int32_t* s_col, const float* s_val,
                                                    int s0, int len,
-                                                   const typename VecOf<VW>::T* __restrict__ Xv,
-                                                   int64_t ldv, int32_t lane_col) {
+                                                   const float* __restrict__ Xl,
+                                                   int64_t ldx) {
   using V = typename VecOf<VW>::T;
   V acc = V(0.0f);
   for (int j = 0; j < len; j += kGatherUnroll) {
@@ -123,7 +150,7 @@ __device__ inline typename VecOf<VW>::T gather_row(const int32_t* s_col, const f
       if (j + u < len) {
         const int p = pad_idx(s0 + j + u);
         a[u] = s_val[p];
-        x[u] = Xv[(int64_t)s_col[p] * ldv + lane_col];
+        x[u] = load_v<VW>(Xl + (int64_t)s_col[p] * ldx);
       }
     }
 #pragma unroll
@@ -141,8 +168,8 @@ __global__ __launch_bounds__(1024) void k_spmm(
     int32_t deg_bound, int32_t W, const int32_t* __restrict__ colidx_s,
     const float* __restrict__ vals_s, const int32_t* __restrict__ perm, const float* __restrict__ X,
     int64_t ldx, float* __restrict__ Y, int64_t ldy, float* __restrict__ ws, int32_t F,
-    int32_t col_base, int32_t slice_cols, int32_t L_rt, int32_t rounds, int32_t cap_pad,
-    int32_t act) {
+    int32_t col_base, int32_t slice_cols, int32_t cols, int32_t L_rt, int32_t rounds,
+    int32_t cap_pad, int32_t act) {
   using V = typename VecOf<VW>::T;
   const int L = LT > 0 ? LT : L_rt;
   extern __shared__ float smem[];
@@ -181,8 +208,7 @@ __global__ __launch_bounds__(1024) void k_spmm(
   }
   __syncthreads();
 
-  const V* __restrict__ Xv = reinterpret_cast<const V*>(X + col0);
-  const int64_t ldxv = ldx / VW;
+  const float* __restrict__ Xs = X + col0;
   if (!hub) {
     const int32_t wn = (int32_t)((uint32_t)info >> 16);
     const int32_t wpr = deg > 0 ? (deg + wn - 1) / wn : 1;  // vwarps per row
@@ -194,10 +220,10 @@ __global__ __launch_bounds__(1024) void k_spmm(
         const int rl = v / wpr, part = v - rl * wpr;
         const int s0 = rl * deg + part * wn;
         const int len = deg > 0 ? min(wn, deg - part * wn) : 0;
-        const V acc = gather_row<VW>(s_col, s_val, s0, len, Xv, ldxv, l);
+        const int lc = lane_col<VW>(l, cols);
+        const V acc = gather_row<VW>(s_col, s_val, s0, len, Xs + lc, ldx);
         if (wpr == 1) {
-          V* yr = reinterpret_cast<V*>(Y + (int64_t)perm[row + rl] * ldy + col0);
-          __builtin_nontemporal_store(act_v(acc, act), yr + l);
+          store_nt<VW>(Y + (int64_t)perm[row + rl] * ldy + col0 + lc, act_v(acc, act));
         } else {
           s_part[part_idx<VW>(v * L + l)] = acc;
         }
@@ -211,8 +237,8 @@ __global__ __launch_bounds__(1024) void k_spmm(
         if (r < rows) {
           V sum = s_part[part_idx<VW>((r * wpr) * L + l)];
           for (int q = 1; q < wpr; ++q) sum += s_part[part_idx<VW>((r * wpr + q) * L + l)];
-          V* yr = reinterpret_cast<V*>(Y + (int64_t)perm[row + r] * ldy + col0);
-          __builtin_nontemporal_store(act_v(sum, act), yr + l);
+          store_nt<VW>(Y + (int64_t)perm[row + r] * ldy + col0 + lane_col<VW>(l, cols),
+                       act_v(sum, act));
         }
       }
     }
@@ -225,7 +251,8 @@ __global__ __launch_bounds__(1024) void k_spmm(
         const int s0 = v * sl;
         const int left = n_e - s0;
         const int len = left < 0 ? 0 : (left < sl ? left : sl);
-        s_part[part_idx<VW>(v * L + l)] = gather_row<VW>(s_col, s_val, s0, len, Xv, ldxv, l);
+        s_part[part_idx<VW>(v * L + l)] =
+            gather_row<VW>(s_col, s_val, s0, len, Xs + lane_col<VW>(l, cols), ldx);
       }
     }
     __syncthreads();
@@ -234,8 +261,7 @@ __global__ __launch_bounds__(1024) void k_spmm(
       if (l < L) {
         V sum = s_part[part_idx<VW>(l)];
         for (int v = 1; v < W; ++v) sum += s_part[part_idx<VW>(v * L + l)];
-        V* wr = reinterpret_cast<V*>(ws + (int64_t)(b - hub_first_entry) * F + col0);
-        wr[l] = sum;
+        store_v<VW>(ws + (int64_t)(b - hub_first_entry) * F + col0 + lane_col<VW>(l, cols), sum);
       }
     }
   }
@@ -248,7 +274,8 @@ __global__ __launch_bounds__(1024) void k_hub_reduce(const int32_t* __restrict__
                                                      const float* __restrict__ ws, int32_t F,
                                                      float* __restrict__ Y, int64_t ldy,
                                                      int32_t col_base, int32_t slice_cols,
-                                                     int32_t L, int32_t G, int32_t act) {
+                                                     int32_t cols, int32_t L, int32_t G,
+                                                     int32_t act) {
   using V = typename VecOf<VW>::T;
   extern __shared__ float smem[];
   V* s_acc = reinterpret_cast<V*>(smem);  // [G][L]
@@ -257,13 +284,13 @@ __global__ __launch_bounds__(1024) void k_hub_reduce(const int32_t* __restrict__
   const int32_t c0 = hub_chunk_off[h], c1 = hub_chunk_off[h + 1];
   const int32_t nc = c1 - c0;
   const int g = threadIdx.x / L, l = threadIdx.x - g * L;
+  const int lc = lane_col<VW>(l, cols);
   const int32_t q = (nc + G - 1) / G;
   if (g < G) {
     V acc = V(0.0f);
     const int32_t a = c0 + g * q;
     const int32_t e = a + q < c1 ? a + q : c1;
-    for (int32_t c = a; c < e; ++c)
-      acc += reinterpret_cast<const V*>(ws + (int64_t)c * F + col0)[l];
+    for (int32_t c = a; c < e; ++c) acc += load_v<VW>(ws + (int64_t)c * F + col0 + lc);
     s_acc[g * L + l] = acc;
   }
   __syncthreads();
@@ -271,10 +298,8 @@ __global__ __launch_bounds__(1024) void k_hub_reduce(const int32_t* __restrict__
     if (g < stride) s_acc[g * L + l] += s_acc[(g + stride) * L + l];
     __syncthreads();
   }
-  if (g == 0) {
-    V* yr = reinterpret_cast<V*>(Y + (int64_t)perm[hub_first_row + h] * ldy + col0);
-    __builtin_nontemporal_store(act_v(s_acc[l], act), yr + l);
-  }
+  if (g == 0)
+    store_nt<VW>(Y + (int64_t)perm[hub_first_row + h] * ldy + col0 + lc, act_v(s_acc[l], act));
 }
 
 // Hub rows of at most MC chunks (every hub row of a plan whose maximum degree
@@ -290,12 +315,12 @@ template <int VW, int MC>
 __global__ __launch_bounds__(kFlatThreads) void k_hub_reduce_flat(
     const int32_t* __restrict__ hub_chunk_off, int32_t hub_first_row,
     const int32_t* __restrict__ perm, const float* __restrict__ ws, int32_t F,
-    float* __restrict__ Y, int64_t ldy, int32_t col_base, int32_t slice_cols, int32_t L,
-    int32_t n_hub, int32_t act) {
+    float* __restrict__ Y, int64_t ldy, int32_t col_base, int32_t slice_cols, int32_t cols,
+    int32_t L, int32_t n_hub, int32_t act) {
   using V = typename VecOf<VW>::T;
   const int64_t t = (int64_t)blockIdx.x * kFlatThreads + threadIdx.x;
   const int32_t h = (int32_t)(t / L);
-  const int l = (int)(t - (int64_t)h * L);
+  const int lc = lane_col<VW>((int)(t - (int64_t)h * L), cols);
   if (h >= n_hub) return;
   const int32_t col0 = col_base + (int32_t)blockIdx.y * slice_cols;
   const int32_t c0 = hub_chunk_off[h];
@@ -303,13 +328,12 @@ __global__ __launch_bounds__(kFlatThreads) void k_hub_reduce_flat(
   V part[MC];
 #pragma unroll
   for (int k = 0; k < MC; ++k)
-    if (k < nc) part[k] = reinterpret_cast<const V*>(ws + (int64_t)(c0 + k) * F + col0)[l];
+    if (k < nc) part[k] = load_v<VW>(ws + (int64_t)(c0 + k) * F + col0 + lc);
   V acc = V(0.0f);
 #pragma unroll
   for (int k = 0; k < MC; ++k)
     if (k < nc) acc += part[k];
-  V* yr = reinterpret_cast<V*>(Y + (int64_t)perm[hub_first_row + h] * ldy + col0);
-  __builtin_nontemporal_store(act_v(acc, act), yr + l);
+  store_nt<VW>(Y + (int64_t)perm[hub_first_row + h] * ldy + col0 + lc, act_v(acc, act));
 }
 
 // Hub rows over column windows (plans with a window table, F >= kWinMinF).
@@ -551,7 +575,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_spmm_rows(
     int32_t n_rows, const int32_t* __restrict__ rowptr_s, const int32_t* __restrict__ colidx_s,
     const float* __restrict__ vals_s, const int32_t* __restrict__ perm, const float* __restrict__ X,
     int64_t ldx, float* __restrict__ Y, int64_t ldy, int32_t col_base, int32_t slice_cols,
-    int32_t L_rt, int32_t act) {
+    int32_t cols, int32_t L_rt, int32_t act) {
   using V = typename VecOf<VW>::T;
   const int L = LT > 0 ? LT : L_rt;
   const int64_t t = (int64_t)blockIdx.x * kSmallThreads + threadIdx.x;
@@ -562,8 +586,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_spmm_rows(
   const int32_t a = rowptr_s[r];
   const int32_t d = rowptr_s[r + 1] - a;
   const int32_t col0 = col_base + (int32_t)blockIdx.y * slice_cols;
-  const V* __restrict__ Xv = reinterpret_cast<const V*>(X + col0);
-  const int64_t ldxv = ldx / VW;
+  const int lc = lane_col<VW>(lane, cols);
+  const float* __restrict__ Xl = X + col0 + lc;
   int32_t c[MD];
   float w[MD];
 #pragma unroll
@@ -576,13 +600,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_spmm_rows(
   V x[MD];
 #pragma unroll
   for (int k = 0; k < MD; ++k)
-    if (k < d) x[k] = Xv[(int64_t)c[k] * ldxv + lane];
+    if (k < d) x[k] = load_v<VW>(Xl + (int64_t)c[k] * ldx);
   V acc = V(0.0f);
 #pragma unroll
   for (int k = 0; k < MD; ++k)
     if (k < d) acc = fma_v(w[k], x[k], acc);
-  V* yr = reinterpret_cast<V*>(Y + (int64_t)perm[r] * ldy + col0);
-  __builtin_nontemporal_store(act_v(acc, act), yr + lane);
+  store_nt<VW>(Y + (int64_t)perm[r] * ldy + col0 + lc, act_v(acc, act));
 }
 
 // --- ablation baselines (the paper's Table II) ------------------------------
@@ -639,14 +662,13 @@ __global__ __launch_bounds__(1024) void k_spmm_wl(
     }
   }
   __syncthreads();
-  const V* __restrict__ Xv = reinterpret_cast<const V*>(X + col0);
-  const int64_t ldxv = ldx / VW;
+  const float* __restrict__ Xs = X + col0;
   for (int k = 0; k < rounds; ++k) {
     const int vt = threadIdx.x + k * T;
     const int v = vt / L, l = vt - v * L;
     if (v < nv)
       s_part[part_idx<VW>(v * L + l)] =
-          gather_row<VW>(s_col, s_val, s_meta[v].y - base, s_meta[v].z, Xv, ldxv, l);
+          gather_row<VW>(s_col, s_val, s_meta[v].y - base, s_meta[v].z, Xs + l * VW, ldx);
   }
   __syncthreads();
   for (int k = 0; k < rounds; ++k) {
@@ -751,7 +773,7 @@ __global__ __launch_bounds__(1024) void k_spmm_colloop(
       len = deg > 0 ? min(wn, deg - part * wn) : 0;
     }
     for (int c = lane; c < F; c += 64) {  // the single-warp column loop
-      const float acc = gather_row<1>(s_col, s_val, s0, len, X, ldx, c);
+      const float acc = gather_row<1>(s_col, s_val, s0, len, X + c, ldx);
       if (!hub && wpr == 1)
         __builtin_nontemporal_store(act_v(acc, act), Y + (int64_t)perm[row + rl] * ldy + c);
       else
@@ -825,10 +847,16 @@ struct EntryRange {
   int32_t max_nnz;
 };
 
+// One run of n_slices column slices, the first at column col_base, slice_cols
+// apart, each `cols` wide with L lanes.
+struct Slices {
+  int n, col_base, slice_cols, cols, L;
+};
+
 template <int VW, int LT>
-void launch_spmm(const SpmmArgs& a, int L, int n_slices, int col_base, int slice_cols,
-                 Marks& mk, bool last_part, EntryRange er) {
+void launch_spmm(const SpmmArgs& a, const Slices& sl, Marks& mk, bool last_part, EntryRange er) {
   const agcn_plan* p = a.p;
+  const int L = sl.L;
   const int cap_pad = stage_words(er.max_nnz);
   const int want = p->W * L;
   const int T = std::min(1024, round_up(want, 64));
@@ -837,67 +865,112 @@ void launch_spmm(const SpmmArgs& a, int L, int n_slices, int col_base, int slice
   const int64_t max_grid = (int64_t)(UINT32_MAX / (uint32_t)T);
   for (int64_t e0 = er.begin; e0 < er.end; e0 += max_grid) {
     const int64_t cnt = std::min<int64_t>(max_grid, er.end - e0);
-    dim3 grid((unsigned)cnt, (unsigned)n_slices);
+    dim3 grid((unsigned)cnt, (unsigned)sl.n);
     const hipEvent_t stop = (last_part && e0 + cnt >= er.end) ? mk.stop : nullptr;
     if (mk.start || stop) {
       hipExtLaunchKernelGGL(k_spmm<VW, LT>, grid, dim3(T), (uint32_t)lds, a.st, mk.start, stop, 0,
                             p->meta, p->order, (int32_t)e0, p->hub_first_entry, p->deg_bound, p->W,
                             p->colidx_s, p->vals_s, p->perm, a.X, a.ldx, a.Y, a.ldy, a.ws, a.F,
-                            col_base, slice_cols, L, rounds, cap_pad, a.act);
+                            sl.col_base, sl.slice_cols, sl.cols, L, rounds, cap_pad, a.act);
       mk.start = nullptr;
     } else {
       k_spmm<VW, LT><<<grid, T, lds, a.st>>>(p->meta, p->order, (int32_t)e0, p->hub_first_entry,
                                              p->deg_bound, p->W, p->colidx_s, p->vals_s, p->perm,
-                                             a.X, a.ldx, a.Y, a.ldy, a.ws, a.F, col_base,
-                                             slice_cols, L, rounds, cap_pad, a.act);
+                                             a.X, a.ldx, a.Y, a.ldy, a.ws, a.F, sl.col_base,
+                                             sl.slice_cols, sl.cols, L, rounds, cap_pad, a.act);
     }
   }
 }
 
 template <int VW>
-void dispatch_spmm(const SpmmArgs& a, int L, int n_slices, int col_base, int slice_cols, Marks& mk,
-                   bool last_part, EntryRange er) {
-  switch (L) {
-    case 1: return launch_spmm<VW, 1>(a, L, n_slices, col_base, slice_cols, mk, last_part, er);
-    case 2: return launch_spmm<VW, 2>(a, L, n_slices, col_base, slice_cols, mk, last_part, er);
-    case 4: return launch_spmm<VW, 4>(a, L, n_slices, col_base, slice_cols, mk, last_part, er);
-    case 8: return launch_spmm<VW, 8>(a, L, n_slices, col_base, slice_cols, mk, last_part, er);
-    case 16: return launch_spmm<VW, 16>(a, L, n_slices, col_base, slice_cols, mk, last_part, er);
-    case 32: return launch_spmm<VW, 32>(a, L, n_slices, col_base, slice_cols, mk, last_part, er);
-    case 64: return launch_spmm<VW, 64>(a, L, n_slices, col_base, slice_cols, mk, last_part, er);
-    default: return launch_spmm<VW, 0>(a, L, n_slices, col_base, slice_cols, mk, last_part, er);
+void dispatch_spmm(const SpmmArgs& a, const Slices& sl, Marks& mk, bool last_part, EntryRange er) {
+  switch (sl.L) {
+    case 1: return launch_spmm<VW, 1>(a, sl, mk, last_part, er);
+    case 2: return launch_spmm<VW, 2>(a, sl, mk, last_part, er);
+    case 4: return launch_spmm<VW, 4>(a, sl, mk, last_part, er);
+    case 8: return launch_spmm<VW, 8>(a, sl, mk, last_part, er);
+    case 16: return launch_spmm<VW, 16>(a, sl, mk, last_part, er);
+    case 32: return launch_spmm<VW, 32>(a, sl, mk, last_part, er);
+    case 64: return launch_spmm<VW, 64>(a, sl, mk, last_part, er);
+    default: return launch_spmm<VW, 0>(a, sl, mk, last_part, er);
   }
+}
+// (VW = 1 serves F < 4 only.)
+template <>
+void dispatch_spmm<1>(const SpmmArgs& a, const Slices& sl, Marks& mk, bool last_part,
+                      EntryRange er) {
+  if (sl.L == 1) return launch_spmm<1, 1>(a, sl, mk, last_part, er);
+  if (sl.L == 2) return launch_spmm<1, 2>(a, sl, mk, last_part, er);
+  return launch_spmm<1, 0>(a, sl, mk, last_part, er);
 }
 
 template <int VW, int MC>
-void launch_hub_flat(const SpmmArgs& a, int L, int n_slices, int col_base, int slice_cols) {
+void launch_hub_flat(const SpmmArgs& a, const Slices& sl) {
   const agcn_plan* p = a.p;
-  dim3 grid((unsigned)ceil_div64((int64_t)p->n_hub_rows * L, kFlatThreads), (unsigned)n_slices);
+  dim3 grid((unsigned)ceil_div64((int64_t)p->n_hub_rows * sl.L, kFlatThreads), (unsigned)sl.n);
   k_hub_reduce_flat<VW, MC><<<grid, kFlatThreads, 0, a.st>>>(
-      p->hub_chunk_off, p->hub_first_row, p->perm, a.ws, a.F, a.Y, a.ldy, col_base, slice_cols, L,
-      p->n_hub_rows, a.act);
+      p->hub_chunk_off, p->hub_first_row, p->perm, a.ws, a.F, a.Y, a.ldy, sl.col_base,
+      sl.slice_cols, sl.cols, sl.L, p->n_hub_rows, a.act);
 }
 
 template <int VW>
-void launch_hub(const SpmmArgs& a, int L, int n_slices, int col_base, int slice_cols) {
+void launch_hub(const SpmmArgs& a, const Slices& sl) {
   const agcn_plan* p = a.p;
+  const int L = sl.L;
   // The flat kernel when every hub row has few chunks and the launch covers
-  // several slices (sweep_powerlaw, 7 chunks at most, per launch: 9.5 against
-  // 13.8 us at 8 slices, 6.3 against 7.8 at 4; at 1 and 2 slices the tree's
-  // one workgroup per row was faster, 4.6 against 5.1 and 5.2 against 5.4).
+  // more than 16 lanes a row, in slices of 8 or in one (sweep_powerlaw, 7 chunks
+  // at most, per launch: 9.5 against 13.8 us at 8 slices, 6.3 against 7.8 at 4;
+  // at 1 and 2 slices the tree's one workgroup per row was faster, 4.6 against
+  // 5.1 and 5.2 against 5.4).
   const int64_t max_chunks = ceil_div64(std::max(p->max_deg, 1), p->H);
-  if (max_chunks <= kFlatMaxChunks && n_slices > 2) {
-    if (max_chunks <= 8) return launch_hub_flat<VW, 8>(a, L, n_slices, col_base, slice_cols);
-    if (max_chunks <= 16) return launch_hub_flat<VW, 16>(a, L, n_slices, col_base, slice_cols);
-    return launch_hub_flat<VW, 32>(a, L, n_slices, col_base, slice_cols);
+  if (max_chunks <= kFlatMaxChunks && sl.n * L > 16) {
+    if (max_chunks <= 8) return launch_hub_flat<VW, 8>(a, sl);
+    if (max_chunks <= 16) return launch_hub_flat<VW, 16>(a, sl);
+    return launch_hub_flat<VW, 32>(a, sl);
   }
   int G = 1;
   while (G < 16 && 2 * G * L <= 1024) G *= 2;
   const int T = round_up(G * L, 64);
   const size_t lds = (size_t)G * L * VW * 4;
-  dim3 grid((unsigned)p->n_hub_rows, (unsigned)n_slices);
+  dim3 grid((unsigned)p->n_hub_rows, (unsigned)sl.n);
   k_hub_reduce<VW><<<grid, T, lds, a.st>>>(p->hub_chunk_off, p->hub_first_row, p->perm, a.ws, a.F,
-                                           a.Y, a.ldy, col_base, slice_cols, L, G, a.act);
+                                           a.Y, a.ldy, sl.col_base, sl.slice_cols, sl.cols, L, G,
+                                           a.act);
+}
+
+// Column slices. An X row that starts on a 128-byte line is taken in 32-column
+// slices, one line each (and a narrower last one): fewer lines in play at a
+// time, so more of them stay in L2. Where rows start anywhere, a 128-byte
+// piece lies on two lines, so cutting a row into k slices costs about k more
+// lines per nonzero than taking it whole; one slice then holds up to 256
+// columns (64 lanes). sweep_powerlaw, 32-column slices against one slice:
+// F = 40 282 and 212 us, 48 256 and 212, 100 709 and 505, 136 838 and 688, 200
+// 1191 and 1034; a power-law graph of 1e6 rows, mean degree 20: F = 40 825 and
+// 599, 100 1999 and 1380, 200 3470 and 2505.
+constexpr int kMaxSliceCols = 256;
+
+template <int VW>
+int slice_width(const SpmmArgs& a) {
+  if (VW == 1) return a.F;
+  const bool lines = a.ldx % 32 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 127u) == 0;
+  const int set = slice_cols_setting();
+  if (lines || set != kDefaultSliceCols) return std::min(a.F, set);
+  const int n = (a.F + kMaxSliceCols - 1) / kMaxSliceCols;
+  return std::min(a.F, round_up((a.F + n - 1) / n, 4));
+}
+
+// F in slices of sc_max columns: a run of full ones, then the rest. A rest
+// narrower than VW columns is widened to VW, sharing columns with the slice
+// before it (the same values are written twice).
+template <int VW>
+int make_slices(int F, int sc_max, Slices out[2]) {
+  const int sc = std::min(F, sc_max);
+  const int n_full = F / sc, tail = F - n_full * sc;
+  out[0] = Slices{n_full, 0, sc, sc, (sc + VW - 1) / VW};
+  if (tail == 0) return 1;
+  const int cols = std::max(tail, VW);
+  out[1] = Slices{1, F - cols, sc, cols, (cols + VW - 1) / VW};
+  return 2;
 }
 
 // Runs one phase (aggregation or hub reduction) over all column slices of
@@ -906,18 +979,11 @@ void launch_hub(const SpmmArgs& a, int L, int n_slices, int col_base, int slice_
 template <int VW>
 int run_phase(const SpmmArgs& a, bool hub_phase, Marks& mk, int sc_max, EntryRange er,
               bool last_range) {
-  const int sc = std::min(a.F, sc_max);
-  const int n_full = a.F / sc;
-  const int tail = a.F - n_full * sc;
-  for (int part = 0; part < 2; ++part) {
-    const int n_slices = part == 0 ? n_full : (tail > 0 ? 1 : 0);
-    if (n_slices == 0) continue;
-    const int cols = part == 0 ? sc : tail;
-    const int L = cols / VW;
-    const int col_base = part == 0 ? 0 : n_full * sc;
-    const bool last_part = last_range && (part == 1 || tail == 0);
-    if (hub_phase) launch_hub<VW>(a, L, n_slices, col_base, sc);
-    else dispatch_spmm<VW>(a, L, n_slices, col_base, sc, mk, last_part, er);
+  Slices sl[2];
+  const int n = make_slices<VW>(a.F, sc_max, sl);
+  for (int part = 0; part < n; ++part) {
+    if (hub_phase) launch_hub<VW>(a, sl[part]);
+    else dispatch_spmm<VW>(a, sl[part], mk, last_range && part == n - 1, er);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, hub_phase ? "k_hub_reduce launch" : "k_spmm launch");
   }
@@ -934,55 +1000,42 @@ bool small_path(const agcn_plan* p) {
 }
 
 template <int VW, int LT, int MD>
-void launch_rows_md(const SpmmArgs& a, int L, int n_slices, int col_base, int slice_cols,
-                    Marks& mk, bool last_part) {
+void launch_rows_md(const SpmmArgs& a, const Slices& sl, Marks& mk, bool last_part) {
   const agcn_plan* p = a.p;
-  const int64_t threads = (int64_t)p->n_rows * L;
-  dim3 grid((unsigned)ceil_div64(threads, kSmallThreads), (unsigned)n_slices);
+  const int64_t threads = (int64_t)p->n_rows * sl.L;
+  dim3 grid((unsigned)ceil_div64(threads, kSmallThreads), (unsigned)sl.n);
   const hipEvent_t stop = last_part ? mk.stop : nullptr;
   hipExtLaunchKernelGGL(k_spmm_rows<VW, LT, MD>, grid, dim3(kSmallThreads), 0, a.st, mk.start,
                         stop, 0, p->n_rows, p->rowptr_s, p->colidx_s, p->vals_s, p->perm, a.X,
-                        a.ldx, a.Y, a.ldy, col_base, slice_cols, L, a.act);
+                        a.ldx, a.Y, a.ldy, sl.col_base, sl.slice_cols, sl.cols, sl.L, a.act);
   mk.start = nullptr;
 }
 
 template <int VW, int LT>
-void launch_rows(const SpmmArgs& a, int L, int n_slices, int col_base, int slice_cols, Marks& mk,
-                 bool last_part) {
+void launch_rows(const SpmmArgs& a, const Slices& sl, Marks& mk, bool last_part) {
   // The loops' depth: the maximum degree rounded up to a multiple of kSmallDegStep.
   switch ((std::max(a.p->max_deg, 1) + kSmallDegStep - 1) / kSmallDegStep) {
-    case 1: launch_rows_md<VW, LT, 8>(a, L, n_slices, col_base, slice_cols, mk, last_part); break;
-    case 2: launch_rows_md<VW, LT, 16>(a, L, n_slices, col_base, slice_cols, mk, last_part); break;
-    case 3: launch_rows_md<VW, LT, 24>(a, L, n_slices, col_base, slice_cols, mk, last_part); break;
-    default: launch_rows_md<VW, LT, 32>(a, L, n_slices, col_base, slice_cols, mk, last_part); break;
+    case 1: launch_rows_md<VW, LT, 8>(a, sl, mk, last_part); break;
+    case 2: launch_rows_md<VW, LT, 16>(a, sl, mk, last_part); break;
+    case 3: launch_rows_md<VW, LT, 24>(a, sl, mk, last_part); break;
+    default: launch_rows_md<VW, LT, 32>(a, sl, mk, last_part); break;
   }
 }
 
 template <int VW>
 int run_small(const SpmmArgs& a, Marks& mk) {
-  const int sc = std::min(a.F, VW == 4 ? kDefaultSliceCols : 64);
-  const int n_full = a.F / sc;
-  const int tail = a.F - n_full * sc;
-  for (int part = 0; part < 2; ++part) {
-    const int n_slices = part == 0 ? n_full : (tail > 0 ? 1 : 0);
-    if (n_slices == 0) continue;
-    const int L = (part == 0 ? sc : tail) / VW;
-    const int col_base = part == 0 ? 0 : n_full * sc;
-    const bool last_part = part == 1 || tail == 0;
-    switch (L) {
-      case 4: launch_rows<VW, 4>(a, L, n_slices, col_base, sc, mk, last_part); break;
-      case 8: launch_rows<VW, 8>(a, L, n_slices, col_base, sc, mk, last_part); break;
-      default: launch_rows<VW, 0>(a, L, n_slices, col_base, sc, mk, last_part); break;
+  Slices sl[2];
+  const int n = make_slices<VW>(a.F, slice_width<VW>(a), sl);
+  for (int part = 0; part < n; ++part) {
+    switch (sl[part].L) {
+      case 4: launch_rows<VW, 4>(a, sl[part], mk, part == n - 1); break;
+      case 8: launch_rows<VW, 8>(a, sl[part], mk, part == n - 1); break;
+      default: launch_rows<VW, 0>(a, sl[part], mk, part == n - 1); break;
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_spmm_rows launch");
   }
   return AGCN_OK;
-}
-
-template <int VW>
-int default_slice_cols() {
-  return VW == 4 ? slice_cols_setting() : std::min(64, slice_cols_setting());
 }
 
 // The aggregation over every entry. When the hub chunks run in column order
@@ -994,12 +1047,11 @@ int default_slice_cols() {
 template <int VW>
 int run_aggregation(const SpmmArgs& a, Marks& mk) {
   const agcn_plan* p = a.p;
-  const int sc = default_slice_cols<VW>();
+  const int sc = slice_width<VW>(a);
   const int32_t n_chunks = p->n_hub_rows > 0 ? p->n_entries - p->hub_first_entry : 0;
-  const int wide = VW == 4 ? kHubSliceCols : std::min(64, kHubSliceCols);
-  if (p->hub_wide && n_chunks > 0 && std::min(a.F, wide) > std::min(a.F, sc)) {
+  if (p->hub_wide && n_chunks > 0 && std::min(a.F, kHubSliceCols) > sc) {
     // Hub chunks hold at most H nonzeros, the other entries at most W * Z.
-    int rc = run_phase<VW>(a, false, mk, wide, EntryRange{0, n_chunks, p->H},
+    int rc = run_phase<VW>(a, false, mk, kHubSliceCols, EntryRange{0, n_chunks, p->H},
                            n_chunks == p->n_entries);
     if (rc || n_chunks == p->n_entries) return rc;
     return run_phase<VW>(a, false, mk, sc, EntryRange{n_chunks, p->n_entries, p->deg_bound}, true);
@@ -1016,7 +1068,7 @@ int run_windows(const SpmmArgs& a, Marks& mk, hipEvent_t ev_end) {
   const int32_t n_chunks = p->n_entries - p->hub_first_entry;
   hipError_t e;
   if (n_chunks < p->n_entries) {
-    const int rc = run_phase<4>(a, false, mk, default_slice_cols<4>(),
+    const int rc = run_phase<4>(a, false, mk, slice_width<4>(a),
                                 EntryRange{n_chunks, p->n_entries, p->deg_bound}, true);
     if (rc) return rc;
   } else {  // hub rows only: the marks frame an empty aggregation
@@ -1160,8 +1212,8 @@ int run_colloop(const SpmmArgs& a, Marks& mk, hipEvent_t ev_end) {
       const int cols = std::min(64, a.F - s * 64);
       k_hub_reduce<1><<<dim3((unsigned)p->n_hub_rows, 1), round_up(G * cols, 64),
                         (size_t)G * cols * 4, a.st>>>(p->hub_chunk_off, p->hub_first_row, p->perm,
-                                                      a.ws, a.F, a.Y, a.ldy, s * 64, 64, cols, G,
-                                                      a.act);
+                                                      a.ws, a.F, a.Y, a.ldy, s * 64, 64, cols,
+                                                      cols, G, a.act);
     }
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "k_hub_reduce launch");
   }
@@ -1217,20 +1269,20 @@ int run_spmm(const agcn_plan* p, int32_t F, const float* X, int64_t ldx, float* 
     return vec ? run_warp_level<4>(a, mk, ev_end) : run_warp_level<1>(a, mk, ev_end);
   if (p->flags & AGCN_PLAN_COLUMN_LOOP) return run_colloop(a, mk, ev_end);
   if (small_path(p)) {
-    const int rc = vec ? run_small<4>(a, mk) : run_small<1>(a, mk);
+    const int rc = F >= 4 ? run_small<4>(a, mk) : run_small<1>(a, mk);
     if (rc) return rc;
     if (ev_end && (e = hipEventRecord(ev_end, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     return AGCN_OK;
   }
   const size_t win_ws = vec ? win_workspace_bytes(p, F) : 0;
   if (win_ws > 0 && ws_bytes >= win_ws) return run_windows(a, mk, ev_end);
-  int rc = vec ? run_aggregation<4>(a, mk) : run_aggregation<1>(a, mk);
+  int rc = F >= 4 ? run_aggregation<4>(a, mk) : run_aggregation<1>(a, mk);
   if (rc) return rc;
   Marks none{};
   const EntryRange all{0, p->n_entries, std::max(p->deg_bound, p->H)};
   if (p->n_hub_rows > 0)
-    rc = vec ? run_phase<4>(a, true, none, default_slice_cols<4>(), all, true)
-             : run_phase<1>(a, true, none, default_slice_cols<1>(), all, true);
+    rc = a.F >= 4 ? run_phase<4>(a, true, none, slice_width<4>(a), all, true)
+                  : run_phase<1>(a, true, none, slice_width<1>(a), all, true);
   if (rc) return rc;
   if (ev_end && (e = hipEventRecord(ev_end, st)) != hipSuccess) return hip_fail(e, "hipEventRecord");
   return AGCN_OK;
