@@ -283,8 +283,16 @@ int agcn_linear(int64_t n, int32_t fin, int32_t fout, const float* d_X, int64_t 
 int agcn_gcn_workspace_size(agcn_plan_t plan, int32_t fout, size_t* bytes);
 
 /* One GCNConv layer forward over the plan's graph (Sec. II-A):
- *   H = X W  (agcn_linear into the workspace),  Y = epilogue(A' H)  (the
- *   plan's SpMM with the epilogue fused into its Y writes).
+ *   Y = epilogue(A' (X W)):  H = X W  (agcn_linear into the workspace),
+ *   Y = epilogue(A' H)  (the plan's SpMM with the epilogue fused into its Y
+ *   writes),
+ * or, where the aggregation gathers clearly less at width fin than at fout
+ * (fin < fout, n_rows <= n_cols, a plan without flags and without hub-row
+ * windows, and the workspace below holds it),
+ *   Y = epilogue((A' X) W):  the SpMM of X into the workspace, then the linear
+ *   step with the epilogue. Same sums up to float rounding order; with a W that
+ *   is not finite, rows without nonzeros are 0 in the first order and NaN in
+ *   the second.
  * d_X: n_cols rows of fin floats (stride ldx); d_W: fin x fout (stride ldw);
  * d_Y: n_rows rows of fout floats (stride ldy); d_ws: at least
  * agcn_gcn_workspace_size(plan, fout) bytes, 16-byte aligned, not

@@ -171,9 +171,13 @@ size_t win_workspace_bytes(const agcn_plan* p, int32_t F);
 // Workspace of the hub chunks (and warp-level blocks) at F.
 size_t chunk_workspace_bytes(const agcn_plan* p, int32_t F);
 
-// H = X W on matrix cores (agcn_linear.hip).
+// What one aggregation at width F gathers per nonzero: 128-byte lines of X rows,
+// weighted by what their reuse in L2 loses on wide rows (see its definition).
+double gather_cost(int32_t F, const float* X, int64_t ldx);
+
+// H = act(X W) on matrix cores (agcn_linear.hip).
 int run_linear(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx, const float* W,
-               int64_t ldw, float* H, int64_t ldh, hipStream_t stream);
+               int64_t ldw, float* H, int64_t ldh, hipStream_t stream, int32_t act);
 
 // agcn_spmm_noalloc's workspace: a fixed device array of this many bytes in
 // agcn_spmm.hip; noalloc_scratch returns its address on `device` (the

@@ -29,6 +29,13 @@ namespace agcn {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+
+// The layer's activation where H is the layer's output (act = 1: ReLU, negative
+// values become 0; NaN and -0 pass through).
+__device__ inline float act_v(float v, int32_t act) { return (act && v < 0.0f) ? 0.0f : v; }
+__device__ inline f4 act_v(f4 v, int32_t act) {
+  return act ? f4{act_v(v.x, 1), act_v(v.y, 1), act_v(v.z, 1), act_v(v.w, 1)} : v;
+}
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 // --- X and W as three bf16 parts each ---------------------------------------------
@@ -175,7 +182,7 @@ template <int RB, int NB>
 __device__ inline void sp_store(const f4 (*acc)[NB], int64_t row0, int i, int g, int col0,
                                 int64_t n, int32_t fin, int32_t fout, const float* __restrict__ X,
                                 int64_t ldx, const float* __restrict__ W, int64_t ldw,
-                                float* __restrict__ H, int64_t ldh) {
+                                float* __restrict__ H, int64_t ldh, int32_t act) {
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int64_t row = row0 + rb * 16 + i;
@@ -191,14 +198,14 @@ __device__ inline void sp_store(const f4 (*acc)[NB], int64_t row0, int i, int g,
           float s = 0.0f;
           for (int k = 0; k < fin; ++k)
             s = __builtin_fmaf(X[row * ldx + k], W[(int64_t)k * ldw + col + e], s);
-          H[row * ldh + col + e] = s;
+          H[row * ldh + col + e] = act_v(s, act);
         }
       } else if (col + 3 < fout) {
-        *reinterpret_cast<f4u*>(H + row * ldh + col) = v;
+        *reinterpret_cast<f4u*>(H + row * ldh + col) = act_v(v, act);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (col + e < fout) H[row * ldh + col + e] = v[e];
+          if (col + e < fout) H[row * ldh + col + e] = act_v(v[e], act);
       }
     }
   }
@@ -207,7 +214,7 @@ __device__ inline void sp_store(const f4 (*acc)[NB], int64_t row0, int i, int g,
 template <int RB, int NB, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_linear_split(
     int64_t n, int32_t fin, int32_t fout, int32_t n_ct, const float* __restrict__ X, int64_t ldx,
-    const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh) {
+    const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
   constexpr int T = WAVES * 64, BM = WAVES * RB * 16;
   __shared__ b8 sw[2][3 * NB * 64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -251,7 +258,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_split(
       for (int rb = 0; rb < RB; ++rb) sp_load_x(xr[rb], k0 + kSpK, g, fin, xv[rb]);
     sp_mma<RB, NB>(xf, sw[buf], i, g, acc);
   }
-  sp_store<RB, NB>(acc, row0, i, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh);
+  sp_store<RB, NB>(acc, row0, i, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh, act);
 }
 
 // k_linear_ksplit: few rows leave k_linear_split a handful of workgroups that
@@ -262,7 +269,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_split(
 template <int NB, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
     int64_t n, int32_t fin, int32_t fout, const float* __restrict__ X, int64_t ldx,
-    const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh) {
+    const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
   __shared__ f4 part[WAVES][NB][64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
@@ -302,7 +309,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
   for (int w = 1; w < WAVES; ++w)
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[0][b] += part[w][b][lane];
-  sp_store<1, NB>(acc, row0, i, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh);
+  sp_store<1, NB>(acc, row0, i, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh, act);
 }
 
 // --- W resident in LDS --------------------------------------------------------
@@ -358,7 +365,8 @@ template <int NB>
 __global__ __launch_bounds__(kRwThreads) void k_linear_rw(int64_t n, int32_t fin, int32_t fout,
                                                           const float* __restrict__ X, int64_t ldx,
                                                           const float* __restrict__ W, int64_t ldw,
-                                                          float* __restrict__ H, int64_t ldh) {
+                                                          float* __restrict__ H, int64_t ldh,
+                                                          int32_t act) {
   constexpr int KS = 2, KP = KS * 16, KC = KP / 4, NJ = NB * 16;
   __shared__ __attribute__((aligned(16))) float swt[NJ * KP];
   // 1. W^T into LDS: W row k is read as float4 (4 output columns) and
@@ -404,7 +412,7 @@ __global__ __launch_bounds__(kRwThreads) void k_linear_rw(int64_t n, int32_t fin
     for (int b = 0; b < NB; ++b) {
       const bool ok = row < n && 16 * b + 4 * g < fout;
       const uint32_t off = ok ? base + (uint32_t)(64 * b) : kRwOutOfRange;
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, acc[b]), hr, (int)off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, act_v(acc[b], act)), hr, (int)off, 0, 0);
     }
   };
   // Full rounds: every wave takes n_tiles / n_waves tiles.
@@ -459,7 +467,7 @@ __global__ __launch_bounds__(kRwThreads) void k_linear_rw(int64_t n, int32_t fin
       const bool ok = row < n && 16 * b + 4 * g < fout;
       const uint32_t off = ok ? (uint32_t)(row * ldh4) + (uint32_t)(16 * g) + (uint32_t)(64 * b)
                               : kRwOutOfRange;
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, acc), hr, (int)off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, act_v(acc, act)), hr, (int)off, 0, 0);
     }
   }
 }
@@ -487,16 +495,16 @@ int rw_grid(int64_t n) {
 
 template <int NB>
 int launch_rw(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx, const float* W,
-              int64_t ldw, float* H, int64_t ldh, hipStream_t st) {
+              int64_t ldw, float* H, int64_t ldh, hipStream_t st, int32_t act) {
   k_linear_rw<NB><<<rw_grid<NB>(n), kRwThreads, 0, st>>>(n, fin, fout, X, ldx, W, ldw, H,
-                                                                 ldh);
+                                                             ldh, act);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? AGCN_OK : hip_fail(e, "k_linear_rw launch");
 }
 
 template <int RB, int NB, int WAVES>
 int launch_split(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx, const float* W,
-                 int64_t ldw, float* H, int64_t ldh, hipStream_t st) {
+                 int64_t ldw, float* H, int64_t ldh, hipStream_t st, int32_t act) {
   const int64_t n_rt = ceil_div64(n, WAVES * RB * 16);
   const int32_t n_ct = (int32_t)ceil_div64(fout, NB * 16);
   // Row tiles in groups of 8, one per XCD; a last group may be partly empty.
@@ -507,7 +515,7 @@ int launch_split(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t l
     const int64_t rows = std::min<int64_t>(max_rt * (WAVES * RB * 16), n - row0);
     const int64_t blocks = ceil_div64(ceil_div64(rows, WAVES * RB * 16), 8) * 8 * n_ct;
     k_linear_split<RB, NB, WAVES><<<dim3((unsigned)blocks), WAVES * 64, 0, st>>>(
-        rows, fin, fout, n_ct, X + row0 * ldx, ldx, W, ldw, H + row0 * ldh, ldh);
+        rows, fin, fout, n_ct, X + row0 * ldx, ldx, W, ldw, H + row0 * ldh, ldh, act);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_linear_split launch");
   }
@@ -516,10 +524,10 @@ int launch_split(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t l
 
 template <int NB, int WAVES>
 int launch_ksplit(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx, const float* W,
-                  int64_t ldw, float* H, int64_t ldh, hipStream_t st) {
+                  int64_t ldw, float* H, int64_t ldh, hipStream_t st, int32_t act) {
   k_linear_ksplit<NB, WAVES>
       <<<dim3((unsigned)ceil_div64(n, 16), (unsigned)ceil_div64(fout, NB * 16)), WAVES * 64, 0,
-         st>>>(n, fin, fout, X, ldx, W, ldw, H, ldh);
+         st>>>(n, fin, fout, X, ldx, W, ldw, H, ldh, act);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? AGCN_OK : hip_fail(e, "k_linear_ksplit launch");
 }
@@ -531,7 +539,7 @@ constexpr int64_t kFewGroups = 512;
 }  // namespace
 
 int run_linear(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx, const float* W,
-               int64_t ldw, float* H, int64_t ldh, hipStream_t st) {
+               int64_t ldw, float* H, int64_t ldh, hipStream_t st, int32_t act) {
   if (n == 0 || fout == 0) return AGCN_OK;
   const bool vec = fin % 4 == 0 && fout % 4 == 0 && ldx % 4 == 0 && ldw % 4 == 0 &&
                    aligned16(X) && aligned16(W);
@@ -546,9 +554,9 @@ int run_linear(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx
       const float* Wc = W + c0;
       float* Hc = H + c0;
       int rc;
-      if (w <= 32) rc = launch_rw<2>(n, fin, w, X, ldx, Wc, ldw, Hc, ldh, st);
-      else if (w <= 64) rc = launch_rw<4>(n, fin, w, X, ldx, Wc, ldw, Hc, ldh, st);
-      else rc = launch_rw<8>(n, fin, w, X, ldx, Wc, ldw, Hc, ldh, st);
+      if (w <= 32) rc = launch_rw<2>(n, fin, w, X, ldx, Wc, ldw, Hc, ldh, st, act);
+      else if (w <= 64) rc = launch_rw<4>(n, fin, w, X, ldx, Wc, ldw, Hc, ldh, st, act);
+      else rc = launch_rw<8>(n, fin, w, X, ldx, Wc, ldw, Hc, ldh, st, act);
       if (rc) return rc;
     }
     return AGCN_OK;
@@ -560,32 +568,32 @@ int run_linear(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx
   if (fin > 32 && ceil_div64(n, 16) * ceil_div64(fout, 64) <= 2 * kFewGroups) {
     const bool many = fin > 256;
     if (fout <= 16)
-      return many ? launch_ksplit<1, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st)
-                  : launch_ksplit<1, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
+      return many ? launch_ksplit<1, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act)
+                  : launch_ksplit<1, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
     if (fout <= 32)
-      return many ? launch_ksplit<2, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st)
-                  : launch_ksplit<2, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
-    return many ? launch_ksplit<4, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st)
-                : launch_ksplit<4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
+      return many ? launch_ksplit<2, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act)
+                  : launch_ksplit<2, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+    return many ? launch_ksplit<4, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act)
+                : launch_ksplit<4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
   }
   // The narrowest tile that holds fout (a wider one multiplies padding): 230,000
   // x 128 -> 16 22.1 us with 16 columns and 24.8 with 32; 256 -> 40 with 48.
-  if (fout <= 16) return launch_split<1, 1, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
-  if (fout <= 32) return launch_split<2, 2, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
+  if (fout <= 16) return launch_split<1, 1, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  if (fout <= 32) return launch_split<2, 2, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
   // 64 rows by 64 columns where 128-row tiles are few: 12,000 x 16 -> 128 4.7
   // against 5.0 us, 30,000 x 64 -> 64 5.6 against 6.4.
   if (ceil_div64(n, 128) * ceil_div64(fout, 64) < kFewGroups && fin <= 256)
-    return launch_split<1, 4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
-  if (fout <= 48) return launch_split<2, 3, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
+    return launch_split<1, 4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  if (fout <= 48) return launch_split<2, 3, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
   // 128 x 64 tiles while memory sets the time (64 -> 128: 34.7 us against 37.3 with
   // 128 columns); 128 columns from fin 65 up (128 -> 128: 55.5 against 57.1), and
   // 256 (X cut once for all of them) from fin 256 up where a tile of 256 is over
   // half full (602 -> 256: 399 against 437, 128 -> 256: 81 against 77).
   if (fout <= 64 || fin <= 64)
-    return launch_split<2, 4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
+    return launch_split<2, 4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
   if (fin >= 256 && (fout - 1) % 256 >= 128)
-    return launch_split<2, 16, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
-  return launch_split<1, 8, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st);
+    return launch_split<2, 16, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  return launch_split<1, 8, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
 }
 
 }  // namespace agcn

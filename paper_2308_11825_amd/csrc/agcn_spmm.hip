@@ -959,6 +959,25 @@ int slice_width(const SpmmArgs& a) {
   return std::min(a.F, round_up((a.F + n - 1) / n, 4));
 }
 
+}  // namespace
+
+// Lines of X rows per nonzero at width F: rows that start on lines take
+// ceil(F / 32) of them (a half line counts 0.85: sweep_powerlaw F = 16 84 us, 32
+// 101); rows at multiples of g bytes 1 + (4 F - g) / 128 on average. A whole
+// slice of more than 2.5 lines per row keeps fewer rows in L2 than 32-column
+// slices do, and its lines cost about a quarter more (F = 100 505 us for 4.0
+// lines, 136 688 for 5.1, 40 212 for 2.0).
+double gather_cost(int32_t F, const float* X, int64_t ldx) {
+  int64_t g = 128;
+  while (g > 4 && ((ldx * 4) % g != 0 || reinterpret_cast<uintptr_t>(X) % (uintptr_t)g != 0)) g /= 2;
+  if (g == 128) return F <= 16 ? 0.85 : (double)((F + 31) / 32);
+  const double lines = 1.0 + std::max(0.0, (4.0 * F - (double)g) / 128.0);
+  if (lines <= 1.0) return F <= 16 ? 0.85 : 1.0;
+  return lines > 2.5 ? 1.25 * lines : lines;
+}
+
+namespace {
+
 // F in slices of sc_max columns: a run of full ones, then the rest. A rest
 // narrower than VW columns is widened to VW, sharing columns with the slice
 // before it (the same values are written twice).
