@@ -157,7 +157,7 @@ void agcn_default_params(agcn_plan_params* p);
  * indices the short sort checks before its last relayout, returning while
  * that relayout runs (larger graphs: checked by the relayout, and the call
  * returns after it; the plan is the same either way); AGCN_TEST_TINY=0 keeps
- * graphs of at most 16384 rows and 2^17 nonzeros off the single-workgroup
+ * graphs of at most 16384 rows and 2^18 - 1 nonzeros off the single-workgroup
  * plan (the same plan again).
  *
  * Hub-row windows: when the rows of degree > deg_bound average at least 16

@@ -1407,8 +1407,6 @@ struct TailArgs {
   int32_t key_base;          // the sort's keys are degree - key_base (>= 0)
   const int32_t* tail_keys;  // [T0, n): the tail's degrees and rows in row order
   const int32_t* tail_ids;
-  const int32_t* rowptr_in;  // instead of tail_keys / tail_ids (the whole graph,
-                             // T0 = 0): degrees from the row pointer, rows in order
   const int32_t* offsets;    // the short pass's (digit, tile) starts, or null
   int32_t n_tiles;
   int32_t* keys;             // outputs: sorted degrees, perm, rowptr_s, cls, seg
@@ -1423,25 +1421,119 @@ struct TailArgs {
 };
 
 
+// Class starts, Alg. 2's segment scan and the summary, from the m sorted rows
+// [T0, n) whose degrees key(0 .. m - 1) returns (in LDS, written and
+// synchronised by the caller): the end of either single-workgroup sort. s_cls
+// holds DB + 2 words.
+template <typename Key>
+__device__ inline void plan_classes(const TailArgs& a, int32_t T0, int32_t m, int32_t* s_cls,
+                                    int32_t& s_hub_first_entry, Key key) {
+  const int32_t n = a.n, W = a.W, Z = a.Z, DB = a.DB, H = a.H;
+  const int32_t* __restrict__ offsets = a.offsets;
+  const int32_t n_tiles = a.n_tiles;
+  int32_t* __restrict__ cls = a.cls;
+  int32_t* __restrict__ seg = a.seg;
+  const int t = threadIdx.x;
+  for (int32_t d = t; d <= DB + 1; d += kTailThreads) {
+    int32_t r;
+    if (offsets != nullptr && d <= a.key_base) {
+      r = offsets[(int64_t)d * n_tiles];
+    } else {
+      int32_t lo = 0, hi = m;  // first tail element of degree >= d
+      while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (key(mid) < d) lo = mid + 1; else hi = mid;
+      }
+      r = T0 + lo;
+    }
+    s_cls[d] = r;
+    cls[d] = r;
+  }
+  __syncthreads();
+  const int32_t hub_first_row = s_cls[DB + 1];
+  const int32_t S = DB + 1 + (n - hub_first_row);
+  // Entries per degree class, a class per thread: pattern_of is a loop of
+  // divisions, and four of them one after the other in the scan below took
+  // half of this function's time (12,000 rows: 4.5 us, now 2.6).
+  constexpr int kPer = (kMaxEntryNnz + 1 + kTailThreads - 1) / kTailThreads;
+  int32_t ent[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int32_t q = t + j * kTailThreads;
+    const int32_t cnt = q <= DB ? s_cls[q + 1] - s_cls[q] : 0;
+    ent[j] = 0;
+    if (cnt > 0) {
+      const int32_t br = pattern_of(q, W, Z) & 0xFFFF;
+      ent[j] = (cnt + br - 1) / br;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int32_t q = t + j * kTailThreads;
+    if (q <= DB) s_cls[q] = ent[j];
+  }
+  __syncthreads();
+  int32_t carry = 0;
+  for (int32_t c0 = 0; c0 < S; c0 += kTailThreads * 4) {
+    int32_t v[4], sm = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int32_t q = c0 + t * 4 + r;
+      int32_t x = 0;
+      if (q <= DB) {
+        x = s_cls[q];
+      } else if (q < S) {
+        x = (int32_t)(((uint32_t)key(hub_first_row - T0 + (q - DB - 1)) + (uint32_t)H - 1) /
+                      (uint32_t)H);
+      }
+      v[r] = x;
+      sm += x;
+    }
+    int32_t total;
+    int32_t rs = block_exclusive_scan<kTailThreads>(sm, &total) + carry;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int32_t q = c0 + t * 4 + r;
+      if (q < S) seg[q] = rs;
+      if (q == DB + 1) s_hub_first_entry = rs;
+      rs += v[r];
+    }
+    carry += total;
+  }
+  __syncthreads();
+  if (t == 0) {
+    seg[S] = carry;
+    const int32_t hfe = S > DB + 1 ? s_hub_first_entry : carry;
+    a.info->n_segments = S;
+    a.sum->n_entries = carry;
+    a.sum->hub_first_entry = hfe;
+    a.sum->n_hub_rows = n - hub_first_row;
+    a.sum->hub_first_row = hub_first_row;
+    a.sum->max_deg = a.dmax[0];
+    if (a.publish) {  // every input error is known: k_degree checked the columns
+      a.sum->err = a.err[0];  // final but for kErrRelayout, which k_relayout_fill may raise
+      __threadfence_system();
+      a.sum->done = 1;
+    }
+    __threadfence_system();
+  }
+}
+
 // LDS of the tail's workgroup (int32 words).
 constexpr int kTailLds = 2 * kTailCap + kTailWaves * kRadixBins + kTailWaves + 1;
 
 __device__ inline void tail_block(const TailArgs& a, const TailShape& ts, int32_t* lds) {
-  const int32_t n = a.n, nnz = a.nnz, T0 = ts.T0, W = a.W, Z = a.Z, DB = a.DB, H = a.H;
+  const int32_t n = a.n, nnz = a.nnz, T0 = ts.T0;
   const int32_t* __restrict__ tail_keys = a.tail_keys;
   const int32_t* __restrict__ tail_ids = a.tail_ids;
-  const int32_t* __restrict__ offsets = a.offsets;
-  const int32_t n_tiles = a.n_tiles;
   int32_t* __restrict__ keys = a.keys;
   int32_t* __restrict__ perm = a.perm;
   int32_t* __restrict__ rowptr_s = a.rowptr_s;
-  int32_t* __restrict__ cls = a.cls;
-  int32_t* __restrict__ seg = a.seg;
   int32_t* s_key = lds;                              // kTailCap
   int32_t* s_id = s_key + kTailCap;                  // kTailCap; cls once the tail is written
   int32_t (*s_cnt)[kRadixBins] = reinterpret_cast<int32_t (*)[kRadixBins]>(s_id + kTailCap);
   int32_t* s_wsum = s_id + kTailCap + kTailWaves * kRadixBins;
-  int32_t& s_hub_first_entry = s_wsum[kTailWaves];
   const uint32_t dmask = (1u << ts.width) - 1;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int32_t m = n - T0;
@@ -1453,13 +1545,8 @@ __device__ inline void tail_block(const TailArgs& a, const TailShape& ts, int32_
   for (int j = 0; j < kTailItems; ++j) {
     if (j < rounds) {
       const int32_t e = w0 + j * 64 + lane;
-      if (a.rowptr_in != nullptr) {
-        k[j] = e < m ? a.rowptr_in[e + 1] - a.rowptr_in[e] : 0;
-        id[j] = e;
-      } else {
-        k[j] = e < m ? tail_keys[T0 + e] : 0;
-        id[j] = e < m ? tail_ids[T0 + e] : 0;
-      }
+      k[j] = e < m ? tail_keys[T0 + e] : 0;
+      id[j] = e < m ? tail_ids[T0 + e] : 0;
     }
   }
   for (int p = 0; p < ts.passes; ++p) {
@@ -1561,73 +1648,7 @@ __device__ inline void tail_block(const TailArgs& a, const TailShape& ts, int32_
     }
     if (t == 0) rowptr_s[n] = nnz;
   }
-  // Class starts.
-  int32_t* s_cls = s_id;
-  for (int32_t d = t; d <= DB + 1; d += kTailThreads) {
-    int32_t r;
-    if (offsets != nullptr && d <= a.key_base) {
-      r = offsets[(int64_t)d * n_tiles];
-    } else {
-      int32_t a = 0, b = m;  // first tail element of degree >= d
-      while (a < b) {
-        const int32_t mid = (a + b) >> 1;
-        if (s_key[mid] < d) a = mid + 1; else b = mid;
-      }
-      r = T0 + a;
-    }
-    s_cls[d] = r;
-    cls[d] = r;
-  }
-  __syncthreads();
-  const int32_t hub_first_row = s_cls[DB + 1];
-  const int32_t S = DB + 1 + (n - hub_first_row);
-  int32_t carry = 0;
-  for (int32_t c0 = 0; c0 < S; c0 += kTailThreads * 4) {
-    int32_t v[4], sm = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int32_t q = c0 + t * 4 + r;
-      int32_t x = 0;
-      if (q <= DB) {
-        const int32_t cnt = s_cls[q + 1] - s_cls[q];
-        if (cnt > 0) {
-          const int32_t br = pattern_of(q, W, Z) & 0xFFFF;
-          x = (cnt + br - 1) / br;
-        }
-      } else if (q < S) {
-        x = (int32_t)(((int64_t)s_key[hub_first_row - T0 + (q - DB - 1)] + H - 1) / H);
-      }
-      v[r] = x;
-      sm += x;
-    }
-    int32_t total;
-    int32_t rs = block_exclusive_scan<kTailThreads>(sm, &total) + carry;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int32_t q = c0 + t * 4 + r;
-      if (q < S) seg[q] = rs;
-      if (q == DB + 1) s_hub_first_entry = rs;
-      rs += v[r];
-    }
-    carry += total;
-  }
-  __syncthreads();
-  if (t == 0) {
-    seg[S] = carry;
-    const int32_t hfe = S > DB + 1 ? s_hub_first_entry : carry;
-    a.info->n_segments = S;
-    a.sum->n_entries = carry;
-    a.sum->hub_first_entry = hfe;
-    a.sum->n_hub_rows = n - hub_first_row;
-    a.sum->hub_first_row = hub_first_row;
-    a.sum->max_deg = a.dmax[0];
-    if (a.publish) {  // every input error is known: k_degree checked the columns
-      a.sum->err = a.err[0];  // final but for kErrRelayout, which k_relayout_fill may raise
-      __threadfence_system();
-      a.sum->done = 1;
-    }
-    __threadfence_system();
-  }
+  plan_classes(a, T0, m, s_id, s_wsum[kTailWaves], [&](int32_t i) { return s_key[i]; });
 }
 
 
@@ -1680,23 +1701,45 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_relayout(
 // The plan of a small graph (at most kTinyMaxRows rows and kTinyMaxNnz
 // nonzeros) up to the partition, in one workgroup of kTailThreads, in place of
 // k_degree, the scans and k_scatter_low: the input checked (row pointer and
-// column indices), every row sorted by degree by the tail's code (key base 0,
-// any W and Z), the class starts, the segment scan and the summary with the
-// host's done flag. k_relayout_fill then copies the whole sorted CSR and fills
-// the partition, reading the tail size (all rows) and the lower nonzeros (none)
-// that this kernel leaves in dmax.
-constexpr int32_t kTinyMaxRows = kTailCap;
-constexpr int64_t kTinyMaxNnz = int64_t(1) << 17;
-constexpr int kTinyCheckItems = 16;
+// column indices), every row sorted by degree in LDS (any W and Z), the class
+// starts, the segment scan and the summary with the host's done flag.
+// k_relayout_fill then copies the whole sorted CSR and fills the partition,
+// reading the tail size (all rows) and the lower nonzeros (none) that this
+// kernel leaves in dmax.
+//
+// A row is one LDS word, degree << 14 | row. The stable sort goes in digits of
+// kTinyBits bits: thread t owns c consecutive rows and one 16-bit counter per
+// digit value, counts its rows, and after one exclusive scan over the counters
+// in (digit, thread) order moves its rows to their places one after the other.
+// No ranking inside a wave is needed: an item costs two dependent LDS accesses
+// where a ballot rank over the digit's bits costs about 110 instructions, and
+// one workgroup is bound by its instructions (12,000 rows, degrees up to 600:
+// 20.8 us of the ballot sort's 44.6 us; c is odd, so that the threads' rows lie
+// in different banks). Columns are checked 16 bytes at a time, 16 loads in
+// flight (127,000 nonzeros: 7.0 us at 4 bytes).
+constexpr int32_t kTinyMaxRows = 1 << 14;
+constexpr int64_t kTinyMaxNnz = (int64_t(1) << 18) - 1;  // a degree fits 18 bits
+constexpr int kTinyBits = 5;
+constexpr int kTinyItems = 17;        // rows per thread, at most (odd)
+constexpr int kTinyCheckItems = 16;   // 16-byte column loads in flight per thread
+constexpr int kTinyCnt = (kTailThreads << kTinyBits) / 2;  // counters, in int32 words
+constexpr int kTinyLds = kTinyMaxRows + kTinyCnt + kMaxEntryNnz + 4;
+static_assert(kTinyCnt >= kTinyMaxRows, "the row pointers take the counters' place");
+
+typedef int32_t i4u __attribute__((ext_vector_type(4), aligned(4)));
 
 __global__ __launch_bounds__(kTailThreads) void k_plan_tiny(TailArgs ta, int32_t n_cols,
                                                             const int32_t* __restrict__ rowptr,
                                                             const int32_t* __restrict__ colidx,
                                                             uint32_t* err, int32_t* tickets,
                                                             int32_t* dmax) {
-  __shared__ int32_t lds[kXLds];
+  __shared__ __attribute__((aligned(16))) int32_t lds[kTinyLds];
   __shared__ uint32_t s_err;
-  __shared__ int32_t s_max;
+  __shared__ int32_t s_max, s_hub_first_entry;
+  uint32_t* s_row = reinterpret_cast<uint32_t*>(lds);             // [n] degree << 14 | row
+  uint16_t* s_cnt = reinterpret_cast<uint16_t*>(lds + kTinyMaxRows);  // [digit][thread]
+  int32_t* s_ptr = lds + kTinyMaxRows;                            // [n], after the sort
+  int32_t* s_cls = lds + kTinyMaxRows + kTinyCnt;                 // [DB + 2]
   const int t = threadIdx.x;
   const int32_t n = ta.n;
   const int64_t nnz = ta.nnz;
@@ -1709,7 +1752,7 @@ __global__ __launch_bounds__(kTailThreads) void k_plan_tiny(TailArgs ta, int32_t
   uint32_t e = 0;
   int32_t mx = 0;
 #pragma unroll
-  for (int j = 0; j < kTailItems; ++j) {  // n <= kTailThreads * kTailItems
+  for (int j = 0; j < kTinyMaxRows / kTailThreads; ++j) {
     const int32_t i = j * kTailThreads + t;
     if (i < n) {
       const int32_t a0 = rowptr[i], b0 = rowptr[i + 1];
@@ -1717,19 +1760,25 @@ __global__ __launch_bounds__(kTailThreads) void k_plan_tiny(TailArgs ta, int32_t
       else mx = max(mx, b0 - a0);
       if (i == 0 && a0 != 0) e |= kErrRowptrStart;
       if (i == n - 1 && (int64_t)b0 != nnz) e |= kErrRowptrEnd;
+      s_row[i] = (uint32_t)(b0 - a0) << 14 | (uint32_t)i;
     }
   }
-  for (int64_t k0 = t; k0 < nnz; k0 += (int64_t)kTailThreads * kTinyCheckItems) {
-    int32_t c[kTinyCheckItems];
+  const int32_t quads = (int32_t)(nnz / 4);
+  for (int32_t k0 = t; k0 < quads; k0 += kTailThreads * kTinyCheckItems) {
+    i4u c[kTinyCheckItems];
 #pragma unroll
     for (int u = 0; u < kTinyCheckItems; ++u) {
-      const int64_t k = k0 + (int64_t)u * kTailThreads;
-      c[u] = k < nnz ? colidx[k] : 0;
+      const int32_t k = k0 + u * kTailThreads;
+      c[u] = *reinterpret_cast<const i4u*>(colidx + 4 * (int64_t)(k < quads ? k : k0));
     }
 #pragma unroll
     for (int u = 0; u < kTinyCheckItems; ++u)
-      e |= (uint32_t)c[u] >= (uint32_t)n_cols ? kErrColumn : 0u;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        e |= (uint32_t)c[u][r] >= (uint32_t)n_cols ? kErrColumn : 0u;
   }
+  if (t < nnz - 4 * (int64_t)quads)
+    e |= (uint32_t)colidx[4 * (int64_t)quads + t] >= (uint32_t)n_cols ? kErrColumn : 0u;
   e = wave_or(e);
   mx = wave_max(mx);
   if ((t & 63) == 0) {
@@ -1752,16 +1801,90 @@ __global__ __launch_bounds__(kTailThreads) void k_plan_tiny(TailArgs ta, int32_t
     }
     return;
   }
-  TailShape ts;
-  ts.take = true;
-  ts.m = n;
-  ts.T0 = 0;
-  ts.nnz_low = 0;
-  int bits = 0;
-  while (bits < 31 && (int64_t(1) << bits) <= (int64_t)s_max) ++bits;
-  ts.passes = (bits + 7) / 8;
-  ts.width = ts.passes > 0 ? (bits + ts.passes - 1) / ts.passes : 8;
-  tail_block(ta, ts, lds);
+  const int32_t c = ((n + kTailThreads - 1) / kTailThreads) | 1;
+  const int32_t r0 = t * c;
+  const int32_t mine = min(c, max(0, n - r0));  // this thread's rows
+  for (int shift = 14; (s_max >> (shift - 14)) != 0; shift += kTinyBits) {
+    uint4* z = reinterpret_cast<uint4*>(s_cnt);
+#pragma unroll
+    for (int k = 0; k < kTinyCnt / 4 / kTailThreads; ++k)
+      z[k * kTailThreads + t] = make_uint4(0, 0, 0, 0);
+    uint32_t v[kTinyItems];
+#pragma unroll
+    for (int j = 0; j < kTinyItems; ++j)
+      if (j < mine) v[j] = s_row[r0 + j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kTinyItems; ++j)
+      if (j < mine) {
+        const uint32_t digit = (v[j] >> shift) & ((1u << kTinyBits) - 1);
+        s_cnt[digit * kTailThreads + t] += 1;
+      }
+    __syncthreads();
+    {  // exclusive scan in place: thread t owns 32 consecutive counters
+      uint4* q = reinterpret_cast<uint4*>(s_cnt) + t * 4;
+      uint32_t w[16];
+      int32_t sum = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint4 x = q[k];
+        w[4 * k] = x.x;
+        w[4 * k + 1] = x.y;
+        w[4 * k + 2] = x.z;
+        w[4 * k + 3] = x.w;
+      }
+#pragma unroll
+      for (int k = 0; k < 16; ++k) sum += (int32_t)((w[k] & 0xFFFFu) + (w[k] >> 16));
+      int32_t total;
+      uint32_t run = (uint32_t)block_exclusive_scan<kTailThreads>(sum, &total);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const uint32_t lo = w[k] & 0xFFFFu, hi = w[k] >> 16;
+        w[k] = run | (run + lo) << 16;
+        run += lo + hi;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        q[k] = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kTinyItems; ++j)
+      if (j < mine) {
+        const uint32_t at = ((v[j] >> shift) & ((1u << kTinyBits) - 1)) * kTailThreads + t;
+        const uint32_t pos = s_cnt[at];
+        s_cnt[at] = (uint16_t)(pos + 1);
+        s_row[pos] = v[j];
+      }
+    __syncthreads();
+  }
+  // Row pointers: each thread's rows in turn, then everything out in order.
+  int32_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < kTinyItems; ++j)
+    if (j < mine) sum += (int32_t)(s_row[r0 + j] >> 14);
+  int32_t total;
+  int32_t run = block_exclusive_scan<kTailThreads>(sum, &total);
+#pragma unroll
+  for (int j = 0; j < kTinyItems; ++j)
+    if (j < mine) {
+      s_ptr[r0 + j] = run;
+      run += (int32_t)(s_row[r0 + j] >> 14);
+    }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kTinyMaxRows / kTailThreads; ++j) {
+    const int32_t i = j * kTailThreads + t;
+    if (i < n) {
+      const uint32_t r = s_row[i];
+      ta.perm[i] = (int32_t)(r & 0x3FFFu);
+      ta.keys[i] = (int32_t)(r >> 14);
+      ta.rowptr_s[i] = s_ptr[i];
+    }
+  }
+  if (t == 0) ta.rowptr_s[n] = (int32_t)nnz;
+  plan_classes(ta, 0, n, s_cls, s_hub_first_entry,
+               [&](int32_t i) { return (int32_t)(s_row[i] >> 14); });
 }
 
 // The summary's error word (the relayout's column check included) and done
@@ -2465,7 +2588,6 @@ int build_plan_block(agcn_plan* p, const int32_t* d_rowptr, const int32_t* d_col
     ta.key_base = kTailKey;
     ta.tail_keys = keys2;
     ta.tail_ids = ids2;
-    ta.rowptr_in = nullptr;
     ta.offsets = counts;
     ta.n_tiles = (int32_t)n_tiles;
     ta.keys = keys;
@@ -2517,7 +2639,6 @@ int build_plan_block(agcn_plan* p, const int32_t* d_rowptr, const int32_t* d_col
     ta.check_cols = INT32_MAX;  // checked by k_plan_tiny
     ta.publish = 1;
     ta.key_base = 0;
-    ta.rowptr_in = d_rowptr;
     ta.offsets = nullptr;
     ta.keys = keys;
     ta.perm = p->perm;
