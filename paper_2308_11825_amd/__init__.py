@@ -249,8 +249,24 @@ def agcn_last_error() -> str:
 # ---- torch-facing wrapper ----
 
 def _stream_handle(device):
+    """Handle of torch's current stream on `device`: what
+    torch.cuda.current_stream(device).cuda_stream is, without the Stream
+    object (1.9 us of a call of 11; where torch has the raw query)."""
     import torch
-    return torch.cuda.current_stream(device).cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return raw(device.index)
+
+
+def _call(device, fn, *args):
+    """fn(*args) with `device` current (the context only where it is not)."""
+    import torch
+    current = getattr(torch._C, "_cuda_getDevice", None)
+    if current is not None and current() == device.index:
+        return fn(*args)
+    with torch.cuda.device(device):
+        return fn(*args)
 
 
 def _unit_col_stride(t):
@@ -295,18 +311,18 @@ class Plan:
         prm.flags = flags
         self.params = prm
         self._handle = None
-        with torch.cuda.device(self.device):
-            st = stream.cuda_stream if stream is not None else _stream_handle(self.device)
-            self._handle = agcn_plan_create(self.n_rows, self.n_cols, self.nnz, rowptr.data_ptr(),
-                                            colidx.data_ptr() if self.nnz else None,
-                                            vals.data_ptr() if self.nnz else None, prm, st)
-            # The plan's last kernel may still read the inputs: on another
-            # stream, torch's allocator must not reuse their memory before it.
-            if stream is not None:
-                for t in (rowptr, colidx, vals):
-                    t.record_stream(stream)
+        st = stream.cuda_stream if stream is not None else _stream_handle(self.device)
+        self._handle = _call(self.device, agcn_plan_create, self.n_rows, self.n_cols, self.nnz,
+                             rowptr.data_ptr(), colidx.data_ptr() if self.nnz else None,
+                             vals.data_ptr() if self.nnz else None, prm, st)
+        # The plan's last kernel may still read the inputs: on another stream,
+        # torch's allocator must not reuse their memory before it.
+        if stream is not None:
+            for t in (rowptr, colidx, vals):
+                t.record_stream(stream)
         self.stats = agcn_plan_info(self._handle)
         self._ws = {}
+        self._ws_bytes = {}  # F -> workspace bytes: the plan's, fixed
 
     @property
     def handle(self):
@@ -322,7 +338,9 @@ class Plan:
         not needed). One per stream, so executes on different streams never
         share hub-row partials."""
         import torch
-        nb = self.workspace_bytes(F)
+        nb = self._ws_bytes.get(F)
+        if nb is None:
+            nb = self._ws_bytes[F] = self.workspace_bytes(F)
         if nb == 0:
             return None
         key = (F, stream.cuda_stream if stream is not None else _stream_handle(self.device))
@@ -353,10 +371,9 @@ class Plan:
         if ws is None:
             ws = self.workspace(F, stream)
         st = stream.cuda_stream if stream is not None else _stream_handle(self.device)
-        with torch.cuda.device(self.device):
-            agcn_spmm_ex(self.handle, F, X.data_ptr(), _row_stride(X), out.data_ptr(),
-                         _row_stride(out), ws.data_ptr() if ws is not None else None, st,
-                         _EPILOGUES[act])
+        _call(self.device, agcn_spmm_ex, self.handle, F, X.data_ptr(), _row_stride(X),
+              out.data_ptr(), _row_stride(out), ws.data_ptr() if ws is not None else None, st,
+              _EPILOGUES[act])
         return out
 
     def gcn_layer(self, X, W, act="relu", out=None, ws=None, stream=None):
@@ -377,13 +394,15 @@ class Plan:
             raise ValueError("out must be a float32 (n_rows, fout) tensor with unit column stride")
         if ws is None:
             nb = agcn_gcn_workspace_size(self.handle, fout)
-            with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(self.device)):
+            if stream is None:
                 ws = torch.empty((nb + 3) // 4, dtype=torch.float32, device=self.device)
+            else:
+                with torch.cuda.stream(stream):
+                    ws = torch.empty((nb + 3) // 4, dtype=torch.float32, device=self.device)
         st = stream.cuda_stream if stream is not None else _stream_handle(self.device)
-        with torch.cuda.device(self.device):
-            agcn_gcn_layer(self.handle, fin, fout, X.data_ptr(), _row_stride(X), W.data_ptr(),
-                           _row_stride(W), out.data_ptr(), _row_stride(out), ws.data_ptr(), st,
-                           _EPILOGUES[act])
+        _call(self.device, agcn_gcn_layer, self.handle, fin, fout, X.data_ptr(), _row_stride(X),
+              W.data_ptr(), _row_stride(W), out.data_ptr(), _row_stride(out), ws.data_ptr(), st,
+              _EPILOGUES[act])
         return out
 
     def export(self):
@@ -406,6 +425,7 @@ class Plan:
             agcn_plan_destroy(self._handle)
             self._handle = None
         self._ws = {}
+        self._ws_bytes = {}
 
     def __del__(self):
         try:
@@ -430,7 +450,6 @@ def linear(X, W, out=None, stream=None):
     if tuple(out.shape) != (n, fout) or not _unit_col_stride(out) or out.dtype != torch.float32:
         raise ValueError("out must be a float32 (n, fout) tensor with unit column stride")
     st = stream.cuda_stream if stream is not None else _stream_handle(X.device)
-    with torch.cuda.device(X.device):
-        agcn_linear(n, fin, fout, X.data_ptr(), _row_stride(X), W.data_ptr(), _row_stride(W),
-                    out.data_ptr(), _row_stride(out), st)
+    _call(X.device, agcn_linear, n, fin, fout, X.data_ptr(), _row_stride(X), W.data_ptr(),
+          _row_stride(W), out.data_ptr(), _row_stride(out), st)
     return out
