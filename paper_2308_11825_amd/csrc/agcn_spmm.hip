@@ -957,14 +957,28 @@ void launch_hub(const SpmmArgs& a, const Slices& sl) {
 // F = 40 282 and 212 us, 48 256 and 212, 100 709 and 505, 136 838 and 688, 200
 // 1191 and 1034; a power-law graph of 1e6 rows, mean degree 20: F = 40 825 and
 // 599, 100 1999 and 1380, 200 3470 and 2505.
+// Where no row is much longer than the mean (uniform random graphs) and X has
+// more lines per slice than the eight L2s hold, hardly any line is met twice in
+// L2 whatever the slice, and slices of two lines halve the passes over the CSR
+// and the metadata (1e6 rows, mean degree 4 / 20, F = 64: 241 -> 220 and 839 ->
+// 782 us; 3e5 rows, mean 8: 113 -> 110; 1e5 rows, whose slice the L2s share,
+// 33.7 and 34.8; a power-law graph of 1e6 rows, mean 20: 616 and 632). Not past
+// F = 128, where the largest graphs lose: 2.4e6 rows, mean 6, F = 128 1502 ->
+// 1438, 256 3101 -> 3163.
 constexpr int kMaxSliceCols = 256;
+constexpr int64_t kL2Lines = (int64_t)8 * 32768;
 
 template <int VW>
 int slice_width(const SpmmArgs& a) {
   if (VW == 1) return a.F;
   const bool lines = a.ldx % 32 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 127u) == 0;
   const int set = slice_cols_setting();
-  if (lines || set != kDefaultSliceCols) return std::min(a.F, set);
+  if (set != kDefaultSliceCols) return std::min(a.F, set);
+  if (lines) {
+    const agcn_plan* p = a.p;
+    const bool uniform = p->n_hub_rows == 0 && (int64_t)p->max_deg * p->n_rows <= 8 * p->nnz;
+    return std::min(a.F, uniform && p->n_cols > kL2Lines && a.F <= 128 ? 64 : kDefaultSliceCols);
+  }
   const int n = (a.F + kMaxSliceCols - 1) / kMaxSliceCols;
   return std::min(a.F, round_up((a.F + n - 1) / n, 4));
 }

@@ -72,3 +72,21 @@ def test_unaligned_workspace(graphs, F):
     ws = torch.empty(plan.workspace_bytes(F) // 4 + 1, device=DEV)
     assert torch.equal(plan.spmm(X, ws=ws[1:]), plan.spmm(X))
     plan.destroy()
+
+
+@pytest.mark.parametrize("n_rows,lo,hi", [(40000, 6, 10), (40000, 0, 60), (700, 6, 10)])
+@pytest.mark.parametrize("F", [32, 64, 96, 128, 132])
+def test_uniform_rows_over_many_columns(n_rows, lo, hi, F):
+    """Rows of about one length over more columns than the L2s hold lines of
+    (two-line slices on aligned rows), and of uneven length or few: the same
+    bits as on rows that start anywhere."""
+    rng = np.random.default_rng(n_rows + hi)
+    g = graphgen.random_csr(n_rows, 270000, rng.integers(lo, hi + 1, size=n_rows), seed=hi, dupes=True)
+    plan = _plan(g)
+    X = np.random.default_rng(F).standard_normal((g.n_cols, F)).astype(np.float32)
+    Yr, S = oracle.spmm(g.rowptr, g.colidx, g.vals, X, n_cols=g.n_cols, want_scale=True)
+    Xd = _dev(X)
+    Y = plan.spmm(Xd)
+    assert_close(Y.cpu().numpy(), Yr, S, f"F={F}")
+    assert torch.equal(Y, plan.spmm(_place(Xd, 1, 3)))
+    plan.destroy()
