@@ -1,6 +1,6 @@
 """The plan's degree sorts give the same plan.
 
-Graphs of at most 16384 rows and 2^17 nonzeros are planned by one workgroup up
+Graphs of at most 16384 rows and 2^18 - 1 nonzeros are planned by one workgroup up
 to the partition (AGCN_TEST_TINY=0 turns that off). Otherwise, with
 W * Z >= 255, the plan first sorts by min(degree, 255) in one pass and sorts
 the rows of degree >= 255 (the tail, at most 16384 rows) in a single
