@@ -964,12 +964,18 @@ void launch_hub(const SpmmArgs& a, const Slices& sl) {
 // 782 us; 3e5 rows, mean 8: 113 -> 110; 1e5 rows, whose slice the L2s share,
 // 33.7 and 34.8; a power-law graph of 1e6 rows, mean 20: 616 and 632). Not past
 // F = 128, where the largest graphs lose: 2.4e6 rows, mean 6, F = 128 1502 ->
-// 1438, 256 3101 -> 3163.
+// 1438, 256 3101 -> 3163. The rows beside the hub-row windows take them too
+// (rest_only) where they gather an X row kRestReuse times or less on average,
+// whatever their shape (1e6 columns, F = 64, 32 against 64 columns: 1000 hub
+// rows 745 and 732 us per execute, 200 hub rows over 6e5 columns 240 and 230; a
+// power-law graph met 5 times per X row 217 and 212, 9 times 335 and 351; F =
+// 128, 300 hub rows: 802 and 776).
 constexpr int kMaxSliceCols = 256;
 constexpr int64_t kL2Lines = (int64_t)8 * 32768;
+constexpr int64_t kRestReuse = 6;
 
 template <int VW>
-int slice_width(const SpmmArgs& a) {
+int slice_width(const SpmmArgs& a, bool rest_only = false) {
   if (VW == 1) return a.F;
   const bool lines = a.ldx % 32 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 127u) == 0;
   const int set = slice_cols_setting();
@@ -977,7 +983,9 @@ int slice_width(const SpmmArgs& a) {
   if (lines) {
     const agcn_plan* p = a.p;
     const bool uniform = p->n_hub_rows == 0 && (int64_t)p->max_deg * p->n_rows <= 8 * p->nnz;
-    return std::min(a.F, uniform && p->n_cols > kL2Lines && a.F <= 128 ? 64 : kDefaultSliceCols);
+    return std::min(a.F, (uniform || rest_only) && p->n_cols > kL2Lines && a.F <= 128
+                             ? 64
+                             : kDefaultSliceCols);
   }
   const int n = (a.F + kMaxSliceCols - 1) / kMaxSliceCols;
   return std::min(a.F, round_up((a.F + n - 1) / n, 4));
@@ -1111,7 +1119,9 @@ int run_windows(const SpmmArgs& a, Marks& mk, hipEvent_t ev_end) {
   const int32_t n_chunks = p->n_entries - p->hub_first_entry;
   hipError_t e;
   if (n_chunks < p->n_entries) {
-    const int rc = run_phase<4>(a, false, mk, slice_width<4>(a),
+    // A row of c chunks holds more than (c - 1) * H nonzeros.
+    const int64_t rest = p->nnz - (int64_t)(n_chunks - p->n_hub_rows) * p->H;
+    const int rc = run_phase<4>(a, false, mk, slice_width<4>(a, rest <= kRestReuse * p->n_cols),
                                 EntryRange{n_chunks, p->n_entries, p->deg_bound}, true);
     if (rc) return rc;
   } else {  // hub rows only: the marks frame an empty aggregation

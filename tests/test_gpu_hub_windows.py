@@ -328,3 +328,23 @@ def test_gcn_layer_over_the_windows(hub_case):
     H = agcn.linear(_dev(X), _dev(W))
     Y = p.spmm(H, act="relu")
     assert torch.equal(Y, p.gcn_layer(_dev(X), _dev(W), act="relu"))
+
+
+@pytest.mark.parametrize("n_cols", [262144, 262145])
+@pytest.mark.parametrize("F", [64, 96, 128, 132])
+def test_few_other_rows_over_many_columns(n_cols, F):
+    """The rows beside the windows, over about as many columns as the L2s hold
+    lines (two-line slices past that, up to F = 128): the oracle's Y, and the
+    same bits as on X rows that start anywhere in memory."""
+    g = _hub_graph(77, 9000, n_cols, 70, 10000, 14000)
+    plan = _plan(g)
+    X = np.random.default_rng(F).standard_normal((n_cols, F)).astype(np.float32)
+    Yr, S = oracle.spmm(g.rowptr, g.colidx, g.vals, X, n_cols=n_cols, want_scale=True)
+    Xd = _dev(X)
+    Y = plan.spmm(Xd)
+    assert_close(Y.cpu().numpy(), Yr, S, f"F={F}")
+    Xs = torch.empty((n_cols, F + 4), device=DEV)[:, :F]
+    Xs.copy_(Xd)
+    few = torch.from_numpy(np.flatnonzero(np.diff(g.rowptr) <= 8)).to(DEV)
+    assert torch.equal(Y[few], plan.spmm(Xs)[few])
+    plan.destroy()
