@@ -315,10 +315,10 @@ def rocsparse_compare(g, Fs, Xs, Ys, d_rowptr, d_colidx, d_vals, stream, reps):
     return out
 
 
-# Dense matrix peaks: fp32, and bf16 over the six part products that stand for
+# Dense matrix peaks: fp32, and bf16 over the eight part products that stand for
 # one fp32 product in k_linear_split and k_linear_ksplit.
 MFMA_FP32_PEAK_TFLOPS = 157.3
-MFMA_SPLIT_PEAK_TFLOPS = 2500.0 / 6
+MFMA_SPLIT_PEAK_TFLOPS = 2500.0 / 8
 
 
 def linear_kernel_name(fin, fout):
@@ -339,19 +339,9 @@ def linear_kernel(n, fin, fout):
         return f"k_linear_rw<{2 if fout <= 32 else 4 if fout <= 64 else 8}>"
     if fin > 32 and cdiv(n, 16) * cdiv(fout, 64) <= 1024:
         return f"k_linear_ksplit<{1 if fout <= 16 else 2 if fout <= 32 else 4}, {8 if fin > 256 else 4}>"
-    if fout <= 16:
-        return "k_linear_split<1, 1, 4>"
-    if fout <= 32:
-        return "k_linear_split<2, 2, 4>"
-    if cdiv(n, 128) * cdiv(fout, 64) < 512 and fin <= 256:
-        return "k_linear_split<1, 4, 4>"
-    if fout <= 48:
-        return "k_linear_split<2, 3, 4>"
-    if fout <= 64 or fin <= 64:
-        return "k_linear_split<2, 4, 4>"
-    if fin >= 256 and (fout - 1) % 256 >= 128:
-        return "k_linear_split<2, 16, 8>"
-    return "k_linear_split<1, 8, 8>"
+    if fout > 32 and cdiv(n, 128) * cdiv(fout, 64) < 512 and fin <= 256:
+        return "k_linear_split<4, 4>"
+    return f"k_linear_split<{8 if fout > 64 else cdiv(fout, 16)}, 8>"
 
 
 def bench_layer(args):

@@ -262,7 +262,7 @@ int agcn_spmm_noalloc(agcn_plan_t plan, int32_t F, const float* d_X, int64_t ldx
  * floats, stride ldw >= fout; d_H: n rows of fout floats, stride ldh >= fout.
  * All row-major, device memory owned by the caller; H must not overlap X or
  * W. fin = 0 gives H = 0. fp32 accuracy and range: X and W enter the bf16
- * matrix cores as three bf16 parts each (24 bits), six part products added in
+ * matrix cores as three bf16 parts each (24 bits), eight part products added in
  * fp32; elements that are not finite are computed again with an fp32 sum, so
  * infinities and NaN are those of the fp32 product. Any alignment and stride
  * takes the same kernels. For fin < 32 with fin, fout, ldx, ldw and ldh

@@ -4,15 +4,19 @@
 // k_linear_split (any shape) multiplies on the bf16 matrix cores: X and W are
 // cut into three bf16 parts each while they are staged (x = x0 + x1 + x2, each
 // part the rounded rest of the one before, 24 bits in all, so the sum is x
-// itself), and six of the nine part products are added in fp32:
-//   x2 w0, x0 w2, x1 w1, x1 w0, x0 w1, x0 w0     (smallest first).
-// The three left out are at most 2^-25 of |x||w| together. A product of bf16
-// numbers is exact in fp32, and v_mfma_f32_16x16x32_bf16 adds 32 of them with
-// about one rounding (measured: 3.2e-8 against 2.5e-8 for a single rounding),
-// so an element sees 6 fin / 32 roundings where the fp32 matrix instruction
-// makes fin: error against 64 bits 1.5e-7 (fin 128) and 3.7e-7 (fin 602)
-// against 2.0e-7 and 4.4e-7 of the fp32 kernel before it. Six bf16 products
-// cost 6/16 of one fp32 product's matrix time.
+// itself), and eight of the nine part products are added in fp32; the one left
+// out, x2 w2, is at most 2^-34 |x||w|. A product of bf16 numbers is exact in
+// fp32, but v_mfma_f32_16x16x32_bf16 cuts off what falls below the last bit of
+// the accumulator it adds to (single products summed in one chain: relative
+// error 3.5e-8 rms, 1.5e-7 at most, where one rounding makes 2.5e-8 and 6.0e-8).
+// So the products below the leading one share an accumulator of their own (at
+// most 2^-7 of the sum), and x0 w0 starts from zero in every chunk of 32 k and is
+// added by one fp32 add: per element fin / 32 roundings where the fp32 matrix
+// instruction makes fin. 2-norm error against 64 bits, fp32 matrix instruction
+// and now, 40,000 rows: one nonzero per row 2.53e-8 and 2.53e-8 (largest 6.0e-8
+// and 6.0e-8), two 3.1e-8 and 2.6e-8, eight 5.3e-8 and 2.8e-8, dense fin 2
+// 3.1e-8 and 2.6e-8, 33 1.07e-7 and 4.0e-8, 128 2.0e-7 and 5.5e-8, 602 4.4e-7
+// and 9.2e-8. Eight bf16 products cost half of one fp32 product's matrix time.
 // Infinities, NaN and values that round past bf16's range turn the parts into
 // NaN, and so every element they take part in: sp_store recomputes any element
 // that is not finite with a plain fp32 sum, which gives the infinity or NaN
@@ -57,11 +61,14 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 // + 3] of every column block b: one 16-byte store each. 16-byte loads and
 // stores need 4-byte alignment only, so every stride and offset takes this
 // path; a row's last chunk is loaded by elements where it is not whole.
-// Bound (230,000 rows): matrix cores from fin 256 up, memory below. Measured
-// before (fp32 tiles) and now: 602 -> 256 797 -> 399 us (1.07 PFLOP/s of bf16
-// products, what a library's bf16 product of 8192^3 reaches on this card is
-// 1.16), 512 -> 128 312 -> 200, 256 -> 40 65 -> 42, 128 -> 128 73 -> 56,
-// 128 -> 64 39 -> 36, 33 -> 17 22 -> 16.
+// A wave takes 16 rows: with 32 the two accumulators leave 3 waves per SIMD or
+// fewer (1e6 x 64 -> 64 120 us against 109, 64 -> 128 128 against 95, 230,000 x
+// 602 -> 64 184 against 167; with 256 columns a tile spills).
+// Bound (230,000 rows): matrix cores from fin 256 up, memory below. Measured with
+// the fp32 matrix instruction and now: 602 -> 256 797 -> 504 us (1.14 PFLOP/s of
+// bf16 products, what a library's bf16 product of 8192^3 reaches on this card is
+// 1.16), 512 -> 128 280 -> 231, 128 -> 128 71 -> 62, 128 -> 64 41 -> 39, 33 -> 17
+// 22 -> 16; 170,000 x 256 -> 40 63 -> 41; 1e6 x 64 -> 64 101 -> 109.
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
@@ -86,24 +93,28 @@ __device__ inline void split8(const float* v, b8* part) {
   }
 }
 
-// acc += W^T chunk (LDS) * X chunk: per column block its three W parts are read
-// once and used by RB row blocks.
-template <int RB, int NB>
-__device__ inline void sp_mma(const b8 (*xf)[3], const b8* __restrict__ sw, int i, int g,
-                              f4 (*acc)[NB]) {
+// One chunk's eight part products, W parts w and X parts x: the seven small ones
+// are added in `lo` from the smallest up, x0 w0 (sixteen bits each way, so the sum
+// of one is exact) alone; `hi` takes it in one fp32 add per chunk.
+constexpr int kSpLo = 7;
+__device__ constexpr int kSpW[kSpLo] = {1, 2, 2, 0, 1, 1, 0}, kSpX[kSpLo] = {2, 1, 0, 2, 1, 0, 1};
+
+// hi + lo += W^T chunk (LDS) * X chunk, column block by column block.
+template <int NB>
+__device__ inline void sp_mma(const b8* xf, const b8* __restrict__ sw, int i, int g, f4* hi,
+                              f4* lo) {
   const int at = i * 4 + ((g + (i >> 1)) & 3);
+  const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     b8 w[3];
 #pragma unroll
     for (int p = 0; p < 3; ++p) w[p] = sw[p * NB * 64 + b * 64 + at];
-    constexpr int wp[6] = {2, 0, 1, 1, 0, 0}, xp[6] = {0, 2, 1, 0, 1, 0};
+    const f4 top = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[0], xf[0], zero, 0, 0, 0);
 #pragma unroll
-    for (int q = 0; q < 6; ++q)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-        acc[rb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[wp[q]], xf[rb][xp[q]], acc[rb][b],
-                                                             0, 0, 0);
+    for (int q = 0; q < kSpLo; ++q)
+      lo[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[kSpW[q]], xf[kSpX[q]], lo[b], 0, 0, 0);
+    hi[b] += top;
   }
 }
 
@@ -178,44 +189,40 @@ struct WStage {
 // Writes the lane's elements of H. Where a group of four holds a value that is
 // not finite (or adds up to none), its elements are computed again from X and W
 // with one fp32 sum each.
-template <int RB, int NB>
-__device__ inline void sp_store(const f4 (*acc)[NB], int64_t row0, int i, int g, int col0,
-                                int64_t n, int32_t fin, int32_t fout, const float* __restrict__ X,
+template <int NB>
+__device__ inline void sp_store(const f4* acc, int64_t row, int g, int col0, int64_t n,
+                                int32_t fin, int32_t fout, const float* __restrict__ X,
                                 int64_t ldx, const float* __restrict__ W, int64_t ldw,
                                 float* __restrict__ H, int64_t ldh, int32_t act) {
+  if (row >= n) return;
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int64_t row = row0 + rb * 16 + i;
-    if (row >= n) continue;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int col = col0 + 16 * b + 4 * g;
-      f4 v = acc[rb][b];
-      const float m = fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(v.w);
-      if (!(m < __builtin_inff())) {
-        for (int e = 0; e < 4; ++e) {
-          if (col + e >= fout) break;
-          float s = 0.0f;
-          for (int k = 0; k < fin; ++k)
-            s = __builtin_fmaf(X[row * ldx + k], W[(int64_t)k * ldw + col + e], s);
-          H[row * ldh + col + e] = act_v(s, act);
-        }
-      } else if (col + 3 < fout) {
-        *reinterpret_cast<f4u*>(H + row * ldh + col) = act_v(v, act);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (col + e < fout) H[row * ldh + col + e] = act_v(v[e], act);
+  for (int b = 0; b < NB; ++b) {
+    const int col = col0 + 16 * b + 4 * g;
+    const f4 v = acc[b];
+    const float m = fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(v.w);
+    if (!(m < __builtin_inff())) {
+      for (int e = 0; e < 4; ++e) {
+        if (col + e >= fout) break;
+        float s = 0.0f;
+        for (int k = 0; k < fin; ++k)
+          s = __builtin_fmaf(X[row * ldx + k], W[(int64_t)k * ldw + col + e], s);
+        H[row * ldh + col + e] = act_v(s, act);
       }
+    } else if (col + 3 < fout) {
+      *reinterpret_cast<f4u*>(H + row * ldh + col) = act_v(v, act);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (col + e < fout) H[row * ldh + col + e] = act_v(v[e], act);
     }
   }
 }
 
-template <int RB, int NB, int WAVES>
+template <int NB, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_linear_split(
     int64_t n, int32_t fin, int32_t fout, int32_t n_ct, const float* __restrict__ X, int64_t ldx,
     const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
-  constexpr int T = WAVES * 64, BM = WAVES * RB * 16;
+  constexpr int T = WAVES * 64, BM = WAVES * 16;
   __shared__ b8 sw[2][3 * NB * 64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
@@ -223,26 +230,18 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_split(
   const int64_t q = blockIdx.x >> 3;
   const int64_t rt = (q / n_ct) * 8 + (blockIdx.x & 7);
   const int ct = (int)(q % n_ct);
-  const int64_t row0 = rt * BM + wave * RB * 16;
+  const int64_t row = rt * BM + wave * 16 + i;
   const int col0 = ct * NB * 16;
   if (rt * BM >= n) return;
-  const float* xr[RB];
+  const float* xr = X + (row < n ? row : n - 1) * ldx;
+  f4 hi[NB], lo[NB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int64_t row = row0 + rb * 16 + i;
-    xr[rb] = X + (row < n ? row : n - 1) * ldx;
-  }
-  f4 acc[RB][NB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[rb][b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int b = 0; b < NB; ++b) hi[b] = lo[b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   WStage<NB, T> ws;
-  float xv[RB][8];
+  float xv[8];
   if (fin > 0) {  // (fin = 0: H = 0, X and W may be NULL)
     ws.load(W, ldw, col0, fout, 0, fin);
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) sp_load_x(xr[rb], 0, g, fin, xv[rb]);
+    sp_load_x(xr, 0, g, fin, xv);
   }
   int buf = 0;
   for (int k0 = 0; k0 < fin; k0 += kSpK, buf ^= 1) {
@@ -250,15 +249,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_split(
     const bool more = k0 + kSpK < fin;
     if (more) ws.load(W, ldw, col0, fout, k0 + kSpK, fin);
     __syncthreads();
-    b8 xf[RB][3];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) split8(xv[rb], xf[rb]);
-    if (more)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) sp_load_x(xr[rb], k0 + kSpK, g, fin, xv[rb]);
-    sp_mma<RB, NB>(xf, sw[buf], i, g, acc);
+    b8 xf[3];
+    split8(xv, xf);
+    if (more) sp_load_x(xr, k0 + kSpK, g, fin, xv);
+    sp_mma<NB>(xf, sw[buf], i, g, hi, lo);
   }
-  sp_store<RB, NB>(acc, row0, i, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh, act);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) hi[b] += lo[b];
+  sp_store<NB>(hi, row, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh, act);
 }
 
 // k_linear_ksplit: few rows leave k_linear_split a handful of workgroups that
@@ -270,15 +268,15 @@ template <int NB, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
     int64_t n, int32_t fin, int32_t fout, const float* __restrict__ X, int64_t ldx,
     const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
-  __shared__ f4 part[WAVES][NB][64];
+  __shared__ f4 part[WAVES][2][NB][64];  // the waves' hi and lo sums
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
   const int64_t row0 = (int64_t)blockIdx.x * 16;
   const int col0 = (int)blockIdx.y * NB * 16;
   const float* xr = X + min(row0 + i, n - 1) * ldx;
-  f4 acc[1][NB];
+  f4 hi[NB], lo[NB];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) acc[0][b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int b = 0; b < NB; ++b) hi[b] = lo[b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   for (int k0 = wave * kSpK; k0 < fin; k0 += WAVES * kSpK) {
     float xv[8], wv[NB][8];
     sp_load_x(xr, k0, g, fin, xv);
@@ -291,25 +289,35 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
     }
     b8 xf[3];
     split8(xv, xf);
-    constexpr int wp[6] = {2, 0, 1, 1, 0, 0}, xp[6] = {0, 2, 1, 0, 1, 0};
+    const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       b8 w[3];
       split8(wv[b], w);
+      const f4 top = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[0], xf[0], zero, 0, 0, 0);
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
-        acc[0][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[wp[q]], xf[xp[q]], acc[0][b], 0, 0, 0);
+      for (int q = 0; q < kSpLo; ++q)
+        lo[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[kSpW[q]], xf[kSpX[q]], lo[b], 0, 0, 0);
+      hi[b] += top;
     }
   }
 #pragma unroll
-  for (int b = 0; b < NB; ++b) part[wave][b][lane] = acc[0][b];
+  for (int b = 0; b < NB; ++b) {
+    part[wave][0][b][lane] = hi[b];
+    part[wave][1][b][lane] = lo[b];
+  }
   __syncthreads();
   if (wave != 0) return;
 #pragma unroll
   for (int w = 1; w < WAVES; ++w)
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[0][b] += part[w][b][lane];
-  sp_store<1, NB>(acc, row0, i, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh, act);
+    for (int b = 0; b < NB; ++b) {
+      hi[b] += part[w][0][b][lane];
+      lo[b] += part[w][1][b][lane];
+    }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) hi[b] += lo[b];
+  sp_store<NB>(hi, row0 + i, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh, act);
 }
 
 // --- W resident in LDS --------------------------------------------------------
@@ -502,19 +510,20 @@ int launch_rw(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx,
   return e == hipSuccess ? AGCN_OK : hip_fail(e, "k_linear_rw launch");
 }
 
-template <int RB, int NB, int WAVES>
+template <int NB, int WAVES>
 int launch_split(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx, const float* W,
                  int64_t ldw, float* H, int64_t ldh, hipStream_t st, int32_t act) {
-  const int64_t n_rt = ceil_div64(n, WAVES * RB * 16);
+  constexpr int64_t BM = WAVES * 16;
+  const int64_t n_rt = ceil_div64(n, BM);
   const int32_t n_ct = (int32_t)ceil_div64(fout, NB * 16);
   // Row tiles in groups of 8, one per XCD; a last group may be partly empty.
   const int64_t max_rt = (int64_t)UINT32_MAX / (WAVES * 64) / n_ct / 8 * 8;
   if (max_rt == 0) return fail(AGCN_ERR_UNSUPPORTED, "matrix too large for one launch");
   for (int64_t r0 = 0; r0 < n_rt; r0 += max_rt) {
-    const int64_t row0 = r0 * (WAVES * RB * 16);
-    const int64_t rows = std::min<int64_t>(max_rt * (WAVES * RB * 16), n - row0);
-    const int64_t blocks = ceil_div64(ceil_div64(rows, WAVES * RB * 16), 8) * 8 * n_ct;
-    k_linear_split<RB, NB, WAVES><<<dim3((unsigned)blocks), WAVES * 64, 0, st>>>(
+    const int64_t row0 = r0 * BM;
+    const int64_t rows = std::min<int64_t>(max_rt * BM, n - row0);
+    const int64_t blocks = ceil_div64(ceil_div64(rows, BM), 8) * 8 * n_ct;
+    k_linear_split<NB, WAVES><<<dim3((unsigned)blocks), WAVES * 64, 0, st>>>(
         rows, fin, fout, n_ct, X + row0 * ldx, ldx, W, ldw, H + row0 * ldh, ldh, act);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_linear_split launch");
@@ -576,24 +585,19 @@ int run_linear(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx
     return many ? launch_ksplit<4, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act)
                 : launch_ksplit<4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
   }
-  // The narrowest tile that holds fout (a wider one multiplies padding): 230,000
-  // x 128 -> 16 22.1 us with 16 columns and 24.8 with 32; 256 -> 40 with 48.
-  if (fout <= 16) return launch_split<1, 1, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
-  if (fout <= 32) return launch_split<2, 2, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
   // 64 rows by 64 columns where 128-row tiles are few: 12,000 x 16 -> 128 4.7
   // against 5.0 us, 30,000 x 64 -> 64 5.6 against 6.4.
-  if (ceil_div64(n, 128) * ceil_div64(fout, 64) < kFewGroups && fin <= 256)
-    return launch_split<1, 4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
-  if (fout <= 48) return launch_split<2, 3, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
-  // 128 x 64 tiles while memory sets the time (64 -> 128: 34.7 us against 37.3 with
-  // 128 columns); 128 columns from fin 65 up (128 -> 128: 55.5 against 57.1), and
-  // 256 (X cut once for all of them) from fin 256 up where a tile of 256 is over
-  // half full (602 -> 256: 399 against 437, 128 -> 256: 81 against 77).
-  if (fout <= 64 || fin <= 64)
-    return launch_split<2, 4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
-  if (fin >= 256 && (fout - 1) % 256 >= 128)
-    return launch_split<2, 16, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
-  return launch_split<1, 8, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  if (fout > 32 && ceil_div64(n, 128) * ceil_div64(fout, 64) < kFewGroups && fin <= 256)
+    return launch_split<4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  // The narrowest tile that holds fout (a wider one multiplies padding): 170,000 x
+  // 256 -> 40 40.7 us with 48 columns and 49 with 64; 128 columns past 64, X being
+  // cut once for all of them (230,000 x 128 -> 128 62 against 65 with two of 64,
+  // 602 -> 256 504 against 560).
+  if (fout <= 16) return launch_split<1, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  if (fout <= 32) return launch_split<2, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  if (fout <= 48) return launch_split<3, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  if (fout <= 64) return launch_split<4, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
+  return launch_split<8, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
 }
 
 }  // namespace agcn

@@ -3,10 +3,12 @@
 k split for few rows, unaligned data, and values outside bf16's range.
 
 Tolerance per element: (fin + 12) u |X||W| + fin 2^-133 (u = 2^-24). The parts'
-products are exact; an element sees 6 ceil(fin / 32) matrix instructions, each
-off by at most 2 u of the largest partial sum (at most |X||W|), at most
-fin + 10 u in all for every fin here, and the products left out are below
-2 u; a part below bf16's smallest number is lost, at most 2^-134 each.
+products are exact; an element sees ceil(fin / 32) matrix instructions and as
+many fp32 adds on its leading products, off by at most 2 u and 1 u of the
+largest partial sum (at most |X||W|), which is at most fin + 3 u for every fin
+here; the sums of the small products are below 2^-6 |X||W| and their errors
+below 1 u, the products left out below 2^-34; a part below bf16's smallest
+number is lost, at most 2^-134 each.
 """
 import numpy as np
 import pytest
@@ -90,3 +92,36 @@ def test_linear_infinities_nan_and_extreme_values(n):
     assert np.isnan(H[3, 3]) and np.isinf(H[4, 7]) and np.isfinite(H[6, :11]).all()
     clean = agcn.linear(_dev(X[20:21]), _dev(W)).cpu().numpy()
     assert np.isfinite(np.delete(H[20], 11)).all() and np.isfinite(np.delete(clean[0], 11)).all()
+
+
+def _chain(X, W):
+    """One fp32 rounding per term, in order: what a fused multiply-add makes
+    (a product of two floats is exact in double)."""
+    H = np.zeros((X.shape[0], W.shape[1]), np.float32)
+    for k in range(X.shape[1]):
+        H = (H.astype(np.float64) + X[:, k:k + 1].astype(np.float64) * W[k].astype(np.float64)).astype(np.float32)
+    return H
+
+
+@pytest.mark.parametrize("n", [600, 20000])     # the k split, the tiles
+@pytest.mark.parametrize("fin,nz", [(128, 1), (128, 2), (128, 3), (128, 8), (300, 4), (1, 1), (2, 2), (3, 3),
+                                    (33, 33), (256, 256)])
+def test_linear_error_is_at_most_one_rounding_per_term(n, fin, nz):
+    """Rows of few nonzeros, spread over the chunks, and dense ones: the 2-norm
+    error against 64 bits is at most that of a chain of fused multiply-adds
+    (1.02: the spread of a sample), and an element that is one product is off by
+    at most u for its one rounding plus u / 8 for the seven small sums (each at
+    most 2^-7 of it and off by 2^-23 of itself)."""
+    rng = np.random.default_rng(n + fin + nz)
+    W = rng.standard_normal((fin, 40)).astype(np.float32)
+    X = np.zeros((n, fin), np.float32)
+    at = np.argsort(rng.random((n, fin)), axis=1)[:, :nz]
+    np.put_along_axis(X, at, rng.standard_normal((n, nz)).astype(np.float32), axis=1)
+    H = agcn.linear(_dev(X), _dev(W)).cpu().numpy()
+    ref = X.astype(np.float64) @ W.astype(np.float64)
+    err = np.abs(H - ref)
+    chain = np.linalg.norm(_chain(X, W) - ref)
+    assert np.linalg.norm(err) <= 1.02 * chain, (np.linalg.norm(err) / np.linalg.norm(ref),
+                                                 chain / np.linalg.norm(ref))
+    if nz == 1:
+        assert (err <= 1.125 * U * np.abs(ref)).all(), float((err / np.abs(ref)).max() / U)
