@@ -18,9 +18,9 @@
 // 3.1e-8 and 2.6e-8, 33 1.07e-7 and 4.0e-8, 128 2.0e-7 and 5.5e-8, 602 4.4e-7
 // and 9.2e-8. Eight bf16 products cost half of one fp32 product's matrix time.
 // Infinities, NaN and values that round past bf16's range turn the parts into
-// NaN, and so every element they take part in: sp_store recomputes any element
-// that is not finite with a plain fp32 sum, which gives the infinity or NaN
-// (or finite value) of the fp32 product. bf16 parts below the normal range
+// NaN, and so every element they take part in: any element that is not finite
+// is computed again by the fp32 matrix instruction (sp_redo), which gives the
+// infinity or NaN (or finite value) of the fp32 product. bf16 parts below the normal range
 // are kept by the matrix instruction (checked on the device).
 // k_linear_ksplit is the same product for few rows: the k range is cut over
 // the waves of a workgroup. k_linear_rw (fp32 matrix instruction, W resident
@@ -186,40 +186,108 @@ struct WStage {
   }
 };
 
-// Writes the lane's elements of H. Where a group of four holds a value that is
-// not finite (or adds up to none), its elements are computed again from X and W
-// with one fp32 sum each.
-template <int NB>
-__device__ inline void sp_store(const f4* acc, int64_t row, int g, int col0, int64_t n,
-                                int32_t fin, int32_t fout, const float* __restrict__ X,
-                                int64_t ldx, const float* __restrict__ W, int64_t ldw,
-                                float* __restrict__ H, int64_t ldh, int32_t act) {
-  if (row >= n) return;
+// Four elements of an H row from column col on, those that lie inside it.
+__device__ inline void sp_put(float* __restrict__ Hrow, int col, int32_t fout, f4 v, int32_t act) {
+  if (col + 3 < fout) {
+    *reinterpret_cast<f4u*>(Hrow + col) = act_v(v, act);
+  } else {
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int col = col0 + 16 * b + 4 * g;
-    const f4 v = acc[b];
-    const float m = fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(v.w);
-    if (!(m < __builtin_inff())) {
-      for (int e = 0; e < 4; ++e) {
-        if (col + e >= fout) break;
-        float s = 0.0f;
-        for (int k = 0; k < fin; ++k)
-          s = __builtin_fmaf(X[row * ldx + k], W[(int64_t)k * ldw + col + e], s);
-        H[row * ldh + col + e] = act_v(s, act);
-      }
-    } else if (col + 3 < fout) {
-      *reinterpret_cast<f4u*>(H + row * ldh + col) = act_v(v, act);
-    } else {
+    for (int e = 0; e < 4; ++e)
+      if (col + e < fout) Hrow[col + e] = act_v(v[e], act);
+  }
+}
+
+// The chunk at k0 as the fp32 matrix instruction takes it: instruction e of a
+// chunk multiplies X[row i][k] by W[k][column i of block b], k = k0 + 4 g + (e & 3)
+// + 16 (e >> 2), both zero past fin.
+template <int GB>
+__device__ inline void sp_load_fp32(const float* __restrict__ xr, const float* __restrict__ W,
+                                    int64_t ldw, int col, int32_t fout, int k0, int g, int32_t fin,
+                                    float* xv, float (*wv)[8]) {
+  sp_load_x(xr, k0, g, fin, xv);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (col + e < fout) H[row * ldh + col + e] = act_v(v[e], act);
+  for (int b = 0; b < GB; ++b) {
+    const float* p = W + min(col + 16 * b, fout - 1);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = k0 + 4 * g + (e & 3) + 16 * (e >> 2);
+      const float w = p[(int64_t)min(k, fin - 1) * ldw];
+      wv[b][e] = k < fin ? w : 0.0f;
     }
   }
 }
 
+// Computes the wave's 16 rows again with the fp32 matrix instruction, GB column
+// blocks at a time and only where some lane's bit of `bad` is set, and writes
+// the groups of four whose bit is set. The next chunk is loaded before the
+// current one is multiplied. Where every element is NaN, 230,000 x 602 -> 256
+// takes 1.62 ms and the finite product 0.49 (a serial sum per element in its own
+// lane: 79), 230,000 x 128 -> 128 0.18 and 0.066 (7.5), 3000 x 1000 -> 16 28 and
+// 12 us (445).
+template <int NB>
+__device__ inline void sp_redo(uint32_t bad, const float* __restrict__ xr, int i, int g, int col0,
+                               int32_t fin, int32_t fout, const float* __restrict__ W, int64_t ldw,
+                               float* __restrict__ Hrow, int32_t act) {
+  constexpr int GB = NB % 2 == 0 ? 2 : 1;
+  static_assert(NB % GB == 0, "");
+#pragma unroll 1
+  for (int b0 = 0; b0 < NB; b0 += GB, bad >>= GB) {
+    const uint32_t mine = bad & ((1u << GB) - 1);
+    if (__ballot(mine != 0) == 0) continue;
+    const int cb = col0 + 16 * b0;
+    f4 acc[GB];
+#pragma unroll
+    for (int b = 0; b < GB; ++b) acc[b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    float xv[8], wv[GB][8], xn[8], wn[GB][8];
+    sp_load_fp32<GB>(xr, W, ldw, cb + i, fout, 0, g, fin, xv, wv);
+#pragma unroll 1
+    for (int k0 = 0; k0 < fin; k0 += kSpK) {
+      if (k0 + kSpK < fin)
+        sp_load_fp32<GB>(xr, W, ldw, cb + i, fout, k0 + kSpK, g, fin, xn, wn);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int b = 0; b < GB; ++b)
+          acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[b][e], xv[e], acc[b], 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        xv[e] = xn[e];
+#pragma unroll
+        for (int b = 0; b < GB; ++b) wv[b][e] = wn[b][e];
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < GB; ++b)
+      if (mine >> b & 1) sp_put(Hrow, cb + 16 * b + 4 * g, fout, acc[b], act);
+  }
+}
+
+// Writes the lane's elements of H, and again (sp_redo) the groups of four that
+// hold a value that is not finite or add up to none.
+template <int NB>
+__device__ inline void sp_store(const f4* acc, const float* __restrict__ xr, int64_t row, int i,
+                                int g, int col0, int64_t n, int32_t fin, int32_t fout,
+                                const float* __restrict__ W, int64_t ldw, float* __restrict__ H,
+                                int64_t ldh, int32_t act) {
+  float* Hrow = H + (row < n ? row : n - 1) * ldh;
+  uint32_t bad = 0;
+  if (row < n) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const f4 v = acc[b];
+      const float m = fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(v.w);
+      bad |= (m < __builtin_inff() ? 0u : 1u) << b;
+      sp_put(Hrow, col0 + 16 * b + 4 * g, fout, v, act);
+    }
+  }
+  if (__ballot(bad != 0) != 0)
+    sp_redo<NB>(bad, xr, i, g, col0, fin, fout, W, ldw, Hrow, act);
+}
+
+// (The second launch bound keeps the registers of the rare sp_redo from costing a
+// wave per SIMD: 602 -> 256 566 us without it.)
 template <int NB, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_linear_split(
+__global__ __launch_bounds__(WAVES * 64, NB <= 2 ? 6 : 4) void k_linear_split(
     int64_t n, int32_t fin, int32_t fout, int32_t n_ct, const float* __restrict__ X, int64_t ldx,
     const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
   constexpr int T = WAVES * 64, BM = WAVES * 16;
@@ -256,7 +324,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_split(
   }
 #pragma unroll
   for (int b = 0; b < NB; ++b) hi[b] += lo[b];
-  sp_store<NB>(hi, row, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh, act);
+  sp_store<NB>(hi, xr, row, i, g, col0, n, fin, fout, W, ldw, H, ldh, act);
 }
 
 // k_linear_ksplit: few rows leave k_linear_split a handful of workgroups that
@@ -317,7 +385,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
     }
 #pragma unroll
   for (int b = 0; b < NB; ++b) hi[b] += lo[b];
-  sp_store<NB>(hi, row0 + i, g, col0, n, fin, fout, X, ldx, W, ldw, H, ldh, act);
+  sp_store<NB>(hi, xr, row0 + i, i, g, col0, n, fin, fout, W, ldw, H, ldh, act);
 }
 
 // --- W resident in LDS --------------------------------------------------------

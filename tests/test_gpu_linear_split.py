@@ -125,3 +125,55 @@ def test_linear_error_is_at_most_one_rounding_per_term(n, fin, nz):
                                                  chain / np.linalg.norm(ref))
     if nz == 1:
         assert (err <= 1.125 * U * np.abs(ref)).all(), float((err / np.abs(ref)).max() / U)
+
+
+@pytest.mark.parametrize("n,fin,fout,offset", [(500, 70, 40, 0), (700, 300, 130, 1), (66001, 40, 16, 0),
+                                               (66000, 33, 31, 3), (40003, 100, 200, 0), (70001, 65, 64, 1)])
+def test_linear_scattered_infinities_in_every_tile(n, fin, fout, offset):
+    """Whole rows and single elements that are not finite, in the first, a
+    middle and the last rows and columns of every tile width."""
+    X, W = _xw(n, fin, fout)
+    rng = np.random.default_rng(5)
+    X[rng.integers(0, n, 40), rng.integers(0, fin, 40)] = np.inf
+    X[rng.integers(0, n, 40), rng.integers(0, fin, 40)] = -np.inf
+    X[n - 1, fin - 1], X[0, 0], X[n // 2] = np.nan, -np.inf, np.nan
+    X[17:33] = -np.finfo(np.float32).max      # past bf16's largest; sums overflow
+    W[fin - 1, fout - 1], W[0, 0] = np.inf, -np.inf
+    wb = torch.zeros(fin * (fout + 1) + offset, device=DEV)
+    Wd = wb[offset:].view(fin, fout + 1)[:, :fout]
+    Wd.copy_(_dev(W))
+    H = agcn.linear(_dev(X), Wd).cpu().numpy()
+    rows = np.r_[0:17, 33:n]
+    _check(X[rows], W, H[rows])
+    # sums of values near the largest may pass infinity on the way: where no
+    # order of the sum can, they are the products' sums
+    with np.errstate(over="ignore", invalid="ignore"):
+        fits = np.abs(X[17:33].astype(np.float64)) @ np.abs(W.astype(np.float64)) < 3.4e38
+        ref = X[17:33].astype(np.float64) @ W.astype(np.float64)
+        S = np.abs(X[17:33].astype(np.float64)) @ np.abs(W.astype(np.float64))
+        assert (np.abs(H[17:33] - ref)[fits] <= ((fin + 12) * U * S)[fits]).all()
+        assert not np.isfinite(H[17:33][:, [0, fout - 1]]).any()
+
+
+def test_linear_of_nan_takes_the_time_of_an_fp32_product():
+    """A matrix of NaN (a diverged layer) costs a few times the finite product,
+    not a serial sum per element (which took 160 times as long)."""
+    n, fin, fout = 20000, 602, 256
+    W = torch.randn(fin, fout, device=DEV)
+    H = torch.empty(n, fout, device=DEV)
+
+    def best(X):
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            agcn.linear(X, W, out=H)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    finite = best(torch.randn(n, fin, device=DEV))
+    nan = best(torch.full((n, fin), float("nan"), device=DEV))
+    assert torch.isnan(H).all()
+    assert nan < 12 * finite, (nan, finite)
