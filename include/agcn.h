@@ -263,8 +263,9 @@ int agcn_spmm_noalloc(agcn_plan_t plan, int32_t F, const float* d_X, int64_t ldx
  * All row-major, device memory owned by the caller; H must not overlap X or
  * W. fin = 0 gives H = 0. fp32 accuracy and range: X and W enter the bf16
  * matrix cores as three bf16 parts each (24 bits), eight part products added in
- * fp32; elements that are not finite are computed again with an fp32 sum, so
- * infinities and NaN are those of the fp32 product. Any alignment and stride
+ * fp32; elements that are not finite, and those that a value below 2^-103 or a
+ * result below 2^-100 could have cost bits, are computed again with fp32
+ * products, so range, infinities and NaN are the fp32 product's. Any alignment and stride
  * takes the same kernels. For fin < 32 with fin, fout, ldx, ldw and ldh
  * multiples of 4, X, W and H 16-byte aligned and X and H each under 4 GiB,
  * the fp32 matrix instruction runs instead with W resident on chip. For few

@@ -20,8 +20,12 @@
 // Infinities, NaN and values that round past bf16's range turn the parts into
 // NaN, and so every element they take part in: any element that is not finite
 // is computed again by the fp32 matrix instruction (sp_redo), which gives the
-// infinity or NaN (or finite value) of the fp32 product. bf16 parts below the normal range
-// are kept by the matrix instruction (checked on the device).
+// infinity or NaN (or finite value) of the fp32 product.
+// bf16 has fp32's exponents and ends at 2^-133, so the third part of a value below
+// 2^-109 loses bits, at most 2^-134, whatever the other factor is; and the small
+// products of a sum near 2^-126 lose bits there. The kernels note where a third
+// part is subnormal (values below 2^-103 only), and sp_redo also computes the
+// elements that such a loss could reach (sp_floor) and those below 2^-100.
 // k_linear_ksplit is the same product for few rows: the k range is cut over
 // the waves of a workgroup. k_linear_rw (fp32 matrix instruction, W resident
 // on chip) serves fin < 32, where a chunk of 32 k is partly empty.
@@ -76,7 +80,8 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kSpK = 32;  // k per chunk: one v_mfma_f32_16x16x32_bf16
 
-__device__ inline void split8(const float* v, b8* part) {
+// The three parts of eight values; tiny: some third part is subnormal.
+__device__ inline void split8(const float* v, b8* part, bool& tiny) {
 #pragma unroll
   for (int i = 0; i < 8; i += 2) {
     f2 r = {v[i], v[i + 1]};
@@ -90,6 +95,8 @@ __device__ inline void split8(const float* v, b8* part) {
         r.y -= (float)h.y;
       }
     }
+    constexpr int kSubnormal = 0x90;  // of v_cmp_class: either sign
+    tiny |= __builtin_amdgcn_classf(r.x, kSubnormal) | __builtin_amdgcn_classf(r.y, kSubnormal);
   }
 }
 
@@ -171,20 +178,72 @@ struct WStage {
       }
     }
   }
-  __device__ inline void store(b8* sw) const {
+  __device__ inline void store(b8* sw, bool& tiny) const {
 #pragma unroll
     for (int u = 0; u < N; ++u) {
       const int idx = threadIdx.x + u * T;
       const int c = idx % (NB * 16), g = idx / (NB * 16);
       if (NB * 64 % T == 0 || idx < NB * 64) {
         b8 part[3];
-        split8(v[u], part);
+        split8(v[u], part, tiny);
 #pragma unroll
         for (int p = 0; p < 3; ++p) sw[p * NB * 64 + c * 4 + ((g + (c >> 1)) & 3)] = part[p];
       }
     }
   }
 };
+
+// What a wave has met: bit r: a third part of row r was subnormal, bit 16: one of
+// the W columns was. A wave leaves its word in LDS before a barrier.
+constexpr uint32_t kSpTinyW = 1u << 16;
+__device__ inline uint32_t sp_tiny(bool x_tiny, bool w_tiny) {
+  const uint64_t r = __ballot(x_tiny);
+  const uint32_t rows = (uint32_t)(r | r >> 16 | r >> 32 | r >> 48) & 0xFFFFu;
+  return rows | (__ballot(w_tiny) != 0 ? kSpTinyW : 0u);
+}
+template <int WAVES>
+__device__ inline uint32_t sp_any(const uint32_t* words) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int v = 0; v < WAVES; ++v) m |= words[v];
+  return __builtin_amdgcn_readfirstlane(m);
+}
+
+// By a wave that met some: the magnitude above which an element of the lane's
+// row has lost at most 2^-26 of itself. The third parts' loss is at most 2^-134
+// in each value of the row or of the W columns, times the largest value that it
+// multiplies, fin times. 230,000 x 602 -> 256, 498 us without such values: one tiny
+// weight 531, a seventh of the weights' rows 589, a third of X's rows 757, all of X
+// (every element computed again) 2014.
+template <int NB>
+__device__ inline float sp_floor(uint32_t tiny, const float* __restrict__ xr, int i, int g,
+                                 int col0, int32_t fin, int32_t fout,
+                                 const float* __restrict__ W, int64_t ldw) {
+  float wm = 0.0f, xm = 0.0f;  // (fmaxf drops NaN)
+  if ((tiny & 0xFFFFu) != 0) {
+    const int cols = min(NB * 16, fout - col0);
+    for (int c = threadIdx.x & 63; c < cols; c += 64) {
+      const float* p = W + col0 + c;
+#pragma unroll 8
+      for (int k = 0; k < fin; ++k) wm = fmaxf(wm, fabsf(p[(int64_t)k * ldw]));
+    }
+  }
+  if ((tiny & kSpTinyW) != 0)
+#pragma unroll 2
+    for (int k0 = 0; k0 < fin; k0 += kSpK) {
+      float v[8];
+      sp_load_x(xr, k0, g, fin, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) xm = fmaxf(xm, fabsf(v[e]));
+    }
+#pragma unroll
+  for (int m = 32; m >= 1; m /= 2) {
+    wm = fmaxf(wm, __shfl_xor(wm, m));
+    if (m >= 16) xm = fmaxf(xm, __shfl_xor(xm, m));
+  }
+  return 0x1p-108f * (float)fin *
+         ((tiny >> i & 1 ? wm : 0.0f) + ((tiny & kSpTinyW) != 0 ? xm : 0.0f));
+}
 
 // Four elements of an H row from column col on, those that lie inside it.
 __device__ inline void sp_put(float* __restrict__ Hrow, int col, int32_t fout, f4 v, int32_t act) {
@@ -262,13 +321,16 @@ __device__ inline void sp_redo(uint32_t bad, const float* __restrict__ xr, int i
   }
 }
 
+constexpr uint32_t kSpSmall = ((127u - 100u) << 24) - 1;  // 2 bits(2^-100) - 1
+
 // Writes the lane's elements of H, and again (sp_redo) the groups of four that
-// hold a value that is not finite or add up to none.
+// hold a value that is not finite (or add up to none), below `floor` or so small
+// that its products were subnormal.
 template <int NB>
 __device__ inline void sp_store(const f4* acc, const float* __restrict__ xr, int64_t row, int i,
                                 int g, int col0, int64_t n, int32_t fin, int32_t fout,
                                 const float* __restrict__ W, int64_t ldw, float* __restrict__ H,
-                                int64_t ldh, int32_t act) {
+                                int64_t ldh, int32_t act, float floor) {
   float* Hrow = H + (row < n ? row : n - 1) * ldh;
   uint32_t bad = 0;
   if (row < n) {
@@ -276,7 +338,13 @@ __device__ inline void sp_store(const f4* acc, const float* __restrict__ xr, int
     for (int b = 0; b < NB; ++b) {
       const f4 v = acc[b];
       const float m = fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(v.w);
-      bad |= (m < __builtin_inff() ? 0u : 1u) << b;
+      uint32_t lo = 0xFFFFFFFFu;  // (2 bits(|v|) - 1: zero is the largest)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lo = min(lo, (__float_as_uint(v[e]) << 1) - 1);
+      bad |= (m < __builtin_inff() && lo >= kSpSmall ? 0u : 1u) << b;
+      if (floor > 0.0f)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad |= (fabsf(v[e]) < floor ? 1u : 0u) << b;
       sp_put(Hrow, col0 + 16 * b + 4 * g, fout, v, act);
     }
   }
@@ -292,6 +360,7 @@ __global__ __launch_bounds__(WAVES * 64, NB <= 2 ? 6 : 4) void k_linear_split(
     const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
   constexpr int T = WAVES * 64, BM = WAVES * 16;
   __shared__ b8 sw[2][3 * NB * 64];
+  __shared__ uint32_t s_tiny[WAVES];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
   // The column tiles of a row tile run on one XCD (workgroups go to the XCDs in turn).
@@ -306,6 +375,7 @@ __global__ __launch_bounds__(WAVES * 64, NB <= 2 ? 6 : 4) void k_linear_split(
 #pragma unroll
   for (int b = 0; b < NB; ++b) hi[b] = lo[b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   WStage<NB, T> ws;
+  bool x_tiny = false, w_tiny = false;
   float xv[8];
   if (fin > 0) {  // (fin = 0: H = 0, X and W may be NULL)
     ws.load(W, ldw, col0, fout, 0, fin);
@@ -313,18 +383,30 @@ __global__ __launch_bounds__(WAVES * 64, NB <= 2 ? 6 : 4) void k_linear_split(
   }
   int buf = 0;
   for (int k0 = 0; k0 < fin; k0 += kSpK, buf ^= 1) {
-    ws.store(sw[buf]);
+    ws.store(sw[buf], w_tiny);
     const bool more = k0 + kSpK < fin;
     if (more) ws.load(W, ldw, col0, fout, k0 + kSpK, fin);
+    const uint32_t w_any = sp_tiny(false, w_tiny);
+    if (lane == 0) s_tiny[wave] = w_any;
     __syncthreads();
     b8 xf[3];
-    split8(xv, xf);
+    split8(xv, xf, x_tiny);
     if (more) sp_load_x(xr, k0 + kSpK, g, fin, xv);
     sp_mma<NB>(xf, sw[buf], i, g, hi, lo);
   }
 #pragma unroll
   for (int b = 0; b < NB; ++b) hi[b] += lo[b];
-  sp_store<NB>(hi, xr, row, i, g, col0, n, fin, fout, W, ldw, H, ldh, act);
+  // The lane's place again: kept over the loop, it costs registers (128 columns
+  // spill, and any scratch costs a short tile a quarter: 1e6 x 32 -> 32 41 -> 52 us).
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  const int i2 = t & 15, g2 = (t >> 4) & 3;
+  const int64_t row2 = rt * BM + (t >> 6) * 16 + i2;
+  const float* xr2 = X + (row2 < n ? row2 : n - 1) * ldx;
+  float floor = 0.0f;
+  const uint32_t tiny = sp_tiny(x_tiny, false) | (fin > 0 ? sp_any<WAVES>(s_tiny) : 0u);
+  if (tiny != 0) floor = sp_floor<NB>(tiny, xr2, i2, g2, col0, fin, fout, W, ldw);
+  sp_store<NB>(hi, xr2, row2, i2, g2, col0, n, fin, fout, W, ldw, H, ldh, act, floor);
 }
 
 // k_linear_ksplit: few rows leave k_linear_split a handful of workgroups that
@@ -337,6 +419,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
     int64_t n, int32_t fin, int32_t fout, const float* __restrict__ X, int64_t ldx,
     const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
   __shared__ f4 part[WAVES][2][NB][64];  // the waves' hi and lo sums
+  __shared__ uint32_t s_tiny[WAVES];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
   const int64_t row0 = (int64_t)blockIdx.x * 16;
@@ -345,6 +428,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
   f4 hi[NB], lo[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) hi[b] = lo[b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  bool x_tiny = false, w_tiny = false;
   for (int k0 = wave * kSpK; k0 < fin; k0 += WAVES * kSpK) {
     float xv[8], wv[NB][8];
     sp_load_x(xr, k0, g, fin, xv);
@@ -356,12 +440,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
         wv[b][e] = p[(int64_t)min(k0 + 4 * g + (e & 3) + 16 * (e >> 2), fin - 1) * ldw];
     }
     b8 xf[3];
-    split8(xv, xf);
+    split8(xv, xf, x_tiny);
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       b8 w[3];
-      split8(wv[b], w);
+      split8(wv[b], w, w_tiny);
       const f4 top = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[0], xf[0], zero, 0, 0, 0);
 #pragma unroll
       for (int q = 0; q < kSpLo; ++q)
@@ -374,9 +458,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
     part[wave][0][b][lane] = hi[b];
     part[wave][1][b][lane] = lo[b];
   }
+  const uint32_t mine = sp_tiny(x_tiny, w_tiny);
+  if (lane == 0) s_tiny[wave] = mine;
   __syncthreads();
   if (wave != 0) return;
-#pragma unroll
+  constexpr int kAhead = NB == 4 ? 3 : WAVES;  // (all of them at once spill with 64 columns)
+#pragma unroll kAhead
   for (int w = 1; w < WAVES; ++w)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -385,7 +472,15 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
     }
 #pragma unroll
   for (int b = 0; b < NB; ++b) hi[b] += lo[b];
-  sp_store<NB>(hi, xr, row0 + i, i, g, col0, n, fin, fout, W, ldw, H, ldh, act);
+  int t = threadIdx.x;  // (as in k_linear_split)
+  asm volatile("" : "+v"(t));
+  const int i2 = t & 15, g2 = (t >> 4) & 3;
+  const int64_t row2 = row0 + i2;
+  const float* xr2 = X + (row2 < n ? row2 : n - 1) * ldx;
+  float floor = 0.0f;
+  const uint32_t tiny = sp_any<WAVES>(s_tiny);
+  if (tiny != 0) floor = sp_floor<NB>(tiny, xr2, i2, g2, col0, fin, fout, W, ldw);
+  sp_store<NB>(hi, xr2, row2, i2, g2, col0, n, fin, fout, W, ldw, H, ldh, act, floor);
 }
 
 // --- W resident in LDS --------------------------------------------------------

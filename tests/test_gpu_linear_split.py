@@ -2,13 +2,14 @@
 (edges and remainders), tiles of 16 to 256 columns and 16 to 128 rows, the
 k split for few rows, unaligned data, and values outside bf16's range.
 
-Tolerance per element: (fin + 12) u |X||W| + fin 2^-133 (u = 2^-24). The parts'
+Tolerance per element: (fin + 12) u |X||W| + 8 fin 2^-149 (u = 2^-24). The parts'
 products are exact; an element sees ceil(fin / 32) matrix instructions and as
 many fp32 adds on its leading products, off by at most 2 u and 1 u of the
 largest partial sum (at most |X||W|), which is at most fin + 3 u for every fin
 here; the sums of the small products are below 2^-6 |X||W| and their errors
-below 1 u, the products left out below 2^-34; a part below bf16's smallest
-number is lost, at most 2^-134 each.
+below 1 u, the products left out below 2^-34; bits lost below bf16's smallest
+number are at most 2^-26 of an element that is kept. Each of the eight products
+of a term is off by at most 2^-149 where it is subnormal.
 """
 import numpy as np
 import pytest
@@ -35,7 +36,7 @@ def _check(X, W, H):
         assert np.array_equal(np.isnan(H), np.isnan(ref32))
         assert np.array_equal(H[~finite & ~np.isnan(ref32)], ref32[~finite & ~np.isnan(ref32)])
         err = np.abs(H.astype(np.float64) - ref)[finite]
-    tol = ((fin + 12) * U * S + fin * 2.0 ** -133)[finite]
+    tol = ((fin + 12) * U * S + 8 * fin * 2.0 ** -149)[finite]
     assert (err <= tol).all(), (float((err / tol).max()), X.shape, W.shape)
 
 
@@ -177,3 +178,30 @@ def test_linear_of_nan_takes_the_time_of_an_fp32_product():
     nan = best(torch.full((n, fin), float("nan"), device=DEV))
     assert torch.isnan(H).all()
     assert nan < 12 * finite, (nan, finite)
+
+
+def _scaled(rng, shape, exponent):
+    return np.ldexp(rng.uniform(1.0, 2.0, shape) * rng.choice([-1.0, 1.0], shape), exponent).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,fin,fout", [(600, 70, 40), (500, 300, 130), (20001, 70, 40), (40000, 33, 64),
+                                        (20000, 100, 150), (3000, 40, 7), (70000, 31, 16)])
+def test_linear_of_tiny_values(n, fin, fout):
+    """Values whose third parts fall below bf16's smallest number, with factors that
+    bring the product back to ordinary size: the fp32 bound relative to |X||W|
+    holds for rows that are all tiny, rows that mix tiny and ordinary values,
+    columns of tiny weights, and products near and below the smallest normal."""
+    rng = np.random.default_rng(fin + fout)
+    for ex, ew in [(-103, 60), (-104, 60), (-109, 100), (-112, 100), (-120, 100), (-126, 90), (-135, 120),
+                   (-60, -60), (-62, -63), (-63, -63), (-66, -66), (-100, 0)]:
+        X, W = _scaled(rng, (n, fin), ex), _scaled(rng, (fin, fout), ew)
+        if n % 2 == 0:
+            X[::3] *= rng.random((X[::3].shape)) < 0.03       # few nonzeros, and rows of zeros
+        _check(X, W, agcn.linear(_dev(X), _dev(W)).cpu().numpy())
+        _check(W.T.copy(), X[:fout].T.copy(), agcn.linear(_dev(W.T), _dev(X[:fout].T)).cpu().numpy())
+    # tiny values that meet large weights beside ordinary ones that meet small weights
+    X, W = _scaled(rng, (n, fin), 0), _scaled(rng, (fin, fout), -30)
+    X[1::4, ::3], W[::3, 1::5] = _scaled(rng, X[1::4, ::3].shape, -118), _scaled(rng, W[::3, 1::5].shape, 100)
+    W[:, 0] = _scaled(rng, fin, -122)
+    W[5, 3], X[2, 7] = 1e-40, 1e-41
+    _check(X, W, agcn.linear(_dev(X), _dev(W)).cpu().numpy())
