@@ -389,7 +389,7 @@ __global__ __launch_bounds__(1024) void k_hub_win(
     const int32_t* __restrict__ colidx_s, const float* __restrict__ vals_s,
     const float* __restrict__ X, int64_t ldx, int32_t n_cols, float* __restrict__ ws, int32_t F) {
   constexpr int NR = kWinRowsPerGroup;
-  __shared__ f4 sx[kWinCols * 16];
+  __shared__ f4 sx[(kWinCols + 1) * 16];  // the window, and a row of zeros for masked pairs
   __shared__ int32_t s_lo[kWinRows], s_hi[kWinRows];
   const int32_t hb0 = (int32_t)blockIdx.x * kWinRows;
   const int32_t kg = (int32_t)blockIdx.y;
@@ -406,6 +406,7 @@ __global__ __launch_bounds__(1024) void k_hub_win(
   f4 acc[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) acc[r] = f4(0.0f);
+  if (t < 16) sx[kWinCols * 16 + t] = f4(0.0f);
   uint32_t stray_rows = 0;  // bit r: a pair of row r fell outside its window
   for (int32_t k = k0; k < k1; ++k) {
     __syncthreads();  // the previous window's reads are done
@@ -456,7 +457,9 @@ __global__ __launch_bounds__(1024) void k_hub_win(
           // Steps in fours, up to the longest batch of the wave's four groups: a
           // range's last batch is half empty on average (skewed_hubs, 55 pairs
           // per range: execute 808 -> 775 us at F = 64, 2857 -> 2754 at 256).
-          const int32_t o_u = use ? off : 0, v_u = use ? v_c : 0;
+          // (a masked pair reads the row of zeros: on a row of X, zero times an
+          // infinity would be NaN)
+          const int32_t o_u = use ? off : kWinCols << 8, v_u = use ? v_c : 0;
           const uint64_t in_m = __ballot(in_c);
           const uint32_t any =
               (uint32_t)(in_m | (in_m >> 16) | (in_m >> 32) | (in_m >> 48)) & 0xFFFFu;

@@ -59,3 +59,21 @@ def test_window_batches(F):
     X = np.random.default_rng(F).standard_normal((g.n_cols, F)).astype(np.float32)
     assert np.array_equal(p.spmm(_dev(X)).cpu().numpy().view(np.uint32), Y.view(np.uint32))
     p.destroy()
+
+
+@pytest.mark.parametrize("F", [64, 132])
+def test_masked_pairs_never_meet_x(F):
+    """X rows that open a window hold infinities and NaN. Hub rows that reference
+    none of them stay finite, whatever the lengths of their last batches and of
+    their neighbours', and whether or not their columns ascend; all rows match the
+    oracle, which multiplies stored pairs only."""
+    rows = [r[r % 512 != 0] if k % 3 else r for k, r in enumerate(_rows())]
+    g = _csr(rows)
+    p = _plan(g)
+    assert p.stats.hub_windows == 301
+    X = np.random.default_rng(F).standard_normal((g.n_cols, F)).astype(np.float32)
+    X[0::1024], X[512::1024] = np.inf, np.nan
+    Y = _spmm_check(p, g, F, X=X)
+    free = np.array([k for k, r in enumerate(rows) if not (r % 512 == 0).any()])
+    assert free.size > 50 and np.isfinite(Y[free]).all()
+    p.destroy()
