@@ -291,14 +291,17 @@ int agcn_gcn_workspace_size(agcn_plan_t plan, int32_t fout, size_t* bytes);
  * (fin < fout, n_rows <= n_cols, a plan without flags and without hub-row
  * windows, and the workspace below holds it),
  *   Y = epilogue((A' X) W):  the SpMM of X into the workspace, then the linear
- *   step with the epilogue. Same sums up to float rounding order; with a W that
- *   is not finite, rows without nonzeros are 0 in the first order and NaN in
- *   the second.
+ *   step with the epilogue.
+ * Same sums up to float rounding order, and 0 in rows without nonzeros in both;
+ * where W holds an infinity, an element that the first order makes NaN
+ * (infinities of both signs met) may be infinite in the second. The order
+ * depends on fin, fout and on how X and the workspace lie in memory (whether
+ * rows start on 128-byte lines), not on values.
  * d_X: n_cols rows of fin floats (stride ldx); d_W: fin x fout (stride ldw);
  * d_Y: n_rows rows of fout floats (stride ldy); d_ws: at least
  * agcn_gcn_workspace_size(plan, fout) bytes, 16-byte aligned, not
- * overlapping X, W or Y. Asynchronous on `stream`; two launches (three with
- * hub rows). Errors: those of agcn_linear and agcn_spmm_ex, plus
+ * overlapping X, W or Y. Asynchronous on `stream`; two launches, one more with
+ * hub rows and, in the second order, one more with rows without nonzeros. Errors: those of agcn_linear and agcn_spmm_ex, plus
  * INVALID_ARGUMENT for a missing or misaligned workspace. */
 int agcn_gcn_layer(agcn_plan_t plan, int32_t fin, int32_t fout, const float* d_X, int64_t ldx,
                    const float* d_W, int64_t ldw, float* d_Y, int64_t ldy, void* d_ws,

@@ -648,8 +648,14 @@ int agcn_gcn_layer(agcn_plan_t plan, int32_t fin, int32_t fout, const float* d_X
     if (int rc = spmm_checked(plan, fin, d_X, ldx, H, fin, static_cast<char*>(d_ws) + t_bytes,
                               stream, nullptr, nullptr, nullptr, AGCN_EPILOGUE_NONE))
       return rc;
-    return agcn::run_linear(plan->n_rows, fin, fout, H, fin, d_W, ldw, d_Y, ldy,
-                            static_cast<hipStream_t>(stream), epilogue);
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    if (int rc = agcn::run_linear(plan->n_rows, fin, fout, H, fin, d_W, ldw, d_Y, ldy, st, epilogue))
+      return rc;
+    // Rows without nonzeros are 0 in the other order whatever W holds; 0 times a W
+    // that is not finite is not.
+    const int rc = agcn::zero_empty_rows(plan, fout, d_Y, ldy, st);
+    if (plan->n_empty > 0 && st != plan->stream) agcn::note_use(plan, st);
+    return rc;
   }
   if (int rc = linear_checked(plan->n_cols, fin, fout, d_X, ldx, d_W, ldw, H, fout, stream))
     return rc;

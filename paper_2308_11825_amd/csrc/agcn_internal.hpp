@@ -33,6 +33,7 @@ struct PlanSummary {
   int32_t hub_first_entry;
   int32_t n_hub_rows;
   int32_t hub_first_row;
+  int32_t n_empty;  // rows without nonzeros (the first of the sorted order)
   int32_t max_deg;
   int32_t n_tail;   // rows of degree >= 255 (the short sort's tail)
   int32_t nnz_low;  // nonzeros of the rows of degree < 255
@@ -77,6 +78,7 @@ struct agcn_plan {
   int32_t W = 0, Z = 0, deg_bound = 0, H = 0;
   uint32_t flags = 0;  // AGCN_PLAN_* (0: the block-level method)
   int32_t n_entries = 0, hub_first_entry = 0, n_hub_rows = 0, hub_first_row = 0, max_deg = 0;
+  int32_t n_empty = 0;   // rows without nonzeros: the sorted positions [0, n_empty)
   void* base = nullptr;  // single device allocation holding everything below
   size_t bytes = 0;
   int32_t* perm = nullptr;          // [n_rows]   sorted position -> original row
@@ -156,6 +158,9 @@ inline int64_t warp_level_blocks(const agcn_plan* p) {
 int run_spmm(const agcn_plan* p, int32_t F, const float* X, int64_t ldx, float* Y, int64_t ldy,
              float* ws, size_t ws_bytes, hipStream_t stream, hipEvent_t ev_begin,
              hipEvent_t ev_mid, hipEvent_t ev_end, int32_t act);
+
+// Y = 0 (F columns) in the rows without nonzeros; launches nothing if there are none.
+int zero_empty_rows(const agcn_plan* p, int32_t F, float* Y, int64_t ldy, hipStream_t stream);
 
 // Launch shape of the hub windows at F: n_slices slices of kWinSliceCols
 // columns, n_b batches of kWinRows hub rows, the plan's n_win windows taken G

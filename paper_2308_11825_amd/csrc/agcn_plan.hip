@@ -1341,6 +1341,7 @@ __global__ __launch_bounds__(kThreads) void k_partition_fill(
     sum->hub_first_entry = seg_off[DB + 1];
     sum->n_hub_rows = n - first_hub_row;
     sum->hub_first_row = first_hub_row;
+    sum->n_empty = cls[1];
     sum->max_deg = n > 0 ? deg_s[n - 1] : 0;
     __threadfence_system();
     sum->done = 1;
@@ -1451,6 +1452,7 @@ __device__ inline void plan_classes(const TailArgs& a, int32_t T0, int32_t m, in
   }
   __syncthreads();
   const int32_t hub_first_row = s_cls[DB + 1];
+  const int32_t n_empty = s_cls[1];  // rows of degree 0
   const int32_t S = DB + 1 + (n - hub_first_row);
   // Entries per degree class, a class per thread: pattern_of is a loop of
   // divisions, and four of them one after the other in the scan below took
@@ -1510,6 +1512,7 @@ __device__ inline void plan_classes(const TailArgs& a, int32_t T0, int32_t m, in
     a.sum->hub_first_entry = hfe;
     a.sum->n_hub_rows = n - hub_first_row;
     a.sum->hub_first_row = hub_first_row;
+    a.sum->n_empty = n_empty;
     a.sum->max_deg = a.dmax[0];
     if (a.publish) {  // every input error is known: k_degree checked the columns
       a.sum->err = a.err[0];  // final but for kErrRelayout, which k_relayout_fill may raise
@@ -2734,6 +2737,7 @@ int build_plan_block(agcn_plan* p, const int32_t* d_rowptr, const int32_t* d_col
   p->hub_first_entry = hs->hub_first_entry;
   p->n_hub_rows = hs->n_hub_rows;
   p->hub_first_row = hs->hub_first_row;
+  p->n_empty = hs->n_empty;
   p->max_deg = hs->max_deg;
 
   // Hub chunks in column order: queued after the summary read-back (an

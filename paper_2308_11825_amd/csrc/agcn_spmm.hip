@@ -1291,7 +1291,23 @@ __device__ __align__(256) float scratch[kNoallocScratchBytes / sizeof(float)];
 
 std::mutex g_scratch_mu;
 float* g_scratch_ptr[kMaxDevices] = {};
+__global__ __launch_bounds__(256) void k_zero_rows(int32_t n, const int32_t* __restrict__ perm,
+                                                   float* __restrict__ Y, int64_t ldy,
+                                                   int32_t F) {
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < (int64_t)n * F; t += stride)
+    Y[(int64_t)perm[t / F] * ldy + t % F] = 0.0f;
+}
+
 }  // namespace
+
+int zero_empty_rows(const agcn_plan* p, int32_t F, float* Y, int64_t ldy, hipStream_t stream) {
+  if (p->n_empty == 0) return AGCN_OK;
+  const int64_t blocks = std::min<int64_t>(ceil_div64((int64_t)p->n_empty * F, 256), 4096);
+  k_zero_rows<<<(unsigned)blocks, 256, 0, stream>>>(p->n_empty, p->perm, Y, ldy, F);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? AGCN_OK : hip_fail(e, "k_zero_rows launch");
+}
 
 int noalloc_scratch(int device, float** out) {
   if (device < 0 || device >= kMaxDevices)

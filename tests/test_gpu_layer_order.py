@@ -23,12 +23,17 @@ def graphs():
             "more_rows": _mixed(163, n=9000, n_cols=2500, hub_max=900)}
 
 
+# (The graphs' hub rows would take column windows, and such plans keep the first
+# order: the second is reached without windows only.)
+@pytest.mark.parametrize("windows", ["1", "0"])
 @pytest.mark.parametrize("name", ["square", "fewer_rows", "more_rows"])
 @pytest.mark.parametrize("fin,fout,pad", [(1, 64, 0), (3, 17, 0), (16, 33, 0), (32, 128, 0), (32, 40, 0),
                                           (30, 256, 3), (64, 65, 0), (100, 300, 0), (128, 256, 4)])
-def test_layer_order_by_width(graphs, name, fin, fout, pad):
+def test_layer_order_by_width(graphs, monkeypatch, name, fin, fout, pad, windows):
+    monkeypatch.setenv("AGCN_HUB_WINDOWS", windows)
     g = graphs[name]
     plan = _plan(g)
+    assert (plan.stats.hub_windows > 0) == (windows == "1")
     rng = np.random.default_rng(fin * 1000 + fout)
     X = rng.standard_normal((g.n_cols, fin)).astype(np.float32)
     W = graphgen.weights(fin, fout, seed=fout)
@@ -46,12 +51,20 @@ def test_layer_order_by_width(graphs, name, fin, fout, pad):
         Y2 = plan.gcn_layer(_dev(X), _dev(W), act=act).cpu().numpy()
         if pad == 0:
             assert np.array_equal(Y.view(np.uint32), Y2.view(np.uint32))
+        if windows == "0" and (fin, fout) in ((1, 64), (32, 128), (16, 33), (128, 256)):
+            # whether the order is the one meant: the same kernels called one by one
+            T = _dev(X) if name == "more_rows" else plan.spmm(_dev(X))
+            Z = agcn.linear(T, _dev(W))
+            Z = plan.spmm(Z, act=act) if name == "more_rows" else (Z.relu() if act == "relu" else Z)
+            assert np.array_equal(Y2, Z.cpu().numpy())
     plan.destroy()
 
 
-def test_layer_order_on_another_stream_and_captured(graphs):
+def test_layer_order_on_another_stream_and_captured(graphs, monkeypatch):
+    monkeypatch.setenv("AGCN_HUB_WINDOWS", "0")
     g = graphs["square"]
     plan = _plan(g)
+    assert plan.stats.hub_windows == 0 and int((g.degrees == 0).sum()) > 0
     W = _dev(graphgen.weights(32, 128, seed=5))
     X = torch.randn((g.n_cols, 32), device=DEV)
     Y0 = plan.gcn_layer(X, W)
@@ -89,3 +102,47 @@ def test_layer_argument_errors_do_not_depend_on_the_order(graphs):
             agcn.agcn_gcn_layer(*args)
         assert e.value.status == agcn.AGCN_ERR_INVALID_ARGUMENT
     plan.destroy()
+
+
+@pytest.mark.parametrize("tiny", ["1", "0"])
+@pytest.mark.parametrize("fin,fout", [(32, 128), (30, 256), (128, 32)])
+def test_rows_without_nonzeros_are_zero_whatever_w_holds(graphs, monkeypatch, tiny, fin, fout):
+    """A W that is not finite reaches every row with nonzeros and no other, in
+    both orders, on two plan paths, on another stream and with a padded Y."""
+    monkeypatch.setenv("AGCN_TEST_TINY", tiny)
+    monkeypatch.setenv("AGCN_HUB_WINDOWS", "0")
+    g = graphs["square"]
+    plan = _plan(g)
+    rng = np.random.default_rng(fin)
+    X = _dev(rng.standard_normal((g.n_cols, fin)).astype(np.float32))
+    W = graphgen.weights(fin, fout, seed=fout)
+    W[3, :] = np.nan
+    W = _dev(W)
+    empty = _dev(g.degrees == 0)
+    assert int(empty.sum()) > 100
+    s = torch.cuda.Stream()
+    for act in ("relu", "none"):
+        Yp = torch.full((g.n_rows, fout + 3), 9.0, device=DEV)
+        plan.gcn_layer(X, W, act=act, out=Yp[:, :fout])
+        assert torch.all(Yp[empty, :fout] == 0) and torch.isnan(Yp[~empty, :fout]).all()
+        assert torch.all(Yp[:, fout:] == 9.0)
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            Y = plan.gcn_layer(X, W, act=act)
+        s.synchronize()
+        assert torch.all(Y[empty] == 0) and torch.isnan(Y[~empty]).all()
+    plan.destroy()
+
+
+def test_empty_rows_of_larger_plans_are_zero():
+    """The same through the short sort and through the multi-pass sort (a degree
+    bound below the short sort's)."""
+    deg = np.random.default_rng(7).integers(0, 9, size=60000)
+    g = graphgen.random_csr(60000, 60000, deg, seed=8)
+    empty = _dev(deg == 0)
+    X, W = torch.randn((g.n_cols, 32), device=DEV), torch.full((32, 128), float("inf"), device=DEV)
+    for kw in ({}, {"max_block_waves": 4, "max_wave_nzs": 32}):
+        plan = _plan(g, **kw)
+        Y = plan.gcn_layer(X, W, act="none")
+        assert torch.all(Y[empty] == 0) and not torch.isfinite(Y[~empty]).any()
+        plan.destroy()
