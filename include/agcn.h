@@ -327,8 +327,8 @@ int agcn_plan_export(agcn_plan_t plan, int32_t* h_perm, int32_t* h_rowptr_s,
                      int32_t* h_colidx_s, float* h_vals_s, int32_t* h_meta);
 
 /* Releases the plan without blocking. Its device block is kept in a
- * per-device cache (the last four blocks, 4 GiB in all beyond the newest)
- * together with events that mark the
+ * per-device cache (four blocks: the largest, and the last of the others up to
+ * 4 GiB in all; given back by agcn_release_cached_memory) together with events that mark the
  * plan's last work on every stream that used it: one recorded here on the
  * stream the plan was created on (covering its creation and every call made
  * on that stream), and one per other stream, re-recorded by each agcn_spmm* /

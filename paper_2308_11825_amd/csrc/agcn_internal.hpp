@@ -206,7 +206,7 @@ struct StreamEvent {
 // waits (device-side) on the events that mark the previous owner's last work
 // on other streams; on `stream` itself its own order already puts that work
 // first. Work marked by no event on another stream makes it synchronise the
-// device instead. device_release keeps the block cached (one per device) with
+// device instead. device_release keeps the block cached (a few per device) with
 // those entries and takes ownership of the events; it does not block.
 int device_alloc(int device, size_t bytes, hipStream_t stream, void** out, size_t* got);
 void device_release(int device, void* ptr, size_t bytes, std::vector<StreamEvent> pending);

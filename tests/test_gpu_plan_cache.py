@@ -66,6 +66,28 @@ def test_alternating_sizes_allocate_nothing_new():
     agcn.agcn_release_cached_memory()
 
 
+def test_a_plan_of_over_4_gib_keeps_its_block_between_small_ones():
+    """The largest block stays whatever the others sum to: after the first round
+    neither plan of an alternation allocates."""
+    agcn.agcn_release_cached_memory()
+    n, d = 1_000_000, 600
+    rowptr = torch.arange(n + 1, dtype=torch.int32, device="cuda:0") * d
+    cols = torch.randint(0, n, (n * d,), dtype=torch.int32, device="cuda:0")
+    big = (rowptr, cols, torch.ones(n * d, device="cuda:0"))
+    g = _graph(3000, 8, 2)
+    small = (_dev(g.rowptr), _dev(g.colidx), _dev(g.vals))
+    for k in range(3):
+        for csr in (big, small):
+            before = _free()
+            p = agcn.Plan(*csr)
+            if csr is big:
+                assert p.stats.device_bytes > 4 << 30
+            if k > 0:
+                assert _free() == before, k
+            p.destroy()
+    agcn.agcn_release_cached_memory()
+
+
 def test_calls_with_another_current_device_context_and_stream():
     """Executes inside a stream context run on that stream, as before."""
     g = _graph(2000, 6, 5)
