@@ -926,17 +926,23 @@ void launch_hub_flat(const SpmmArgs& a, const Slices& sl) {
       sl.slice_cols, sl.cols, sl.L, p->n_hub_rows, a.act);
 }
 
+// The flat kernel when every hub row has few chunks and the call's first run of
+// slices covers more than 16 lanes a row, in slices of 8 or in one
+// (sweep_powerlaw, 7 chunks at most, per launch: 9.5 against 13.8 us at 8 slices,
+// 6.3 against 7.8 at 4; at 1 and 2 slices the tree's one workgroup per row was
+// faster, 4.6 against 5.1 and 5.2 against 5.4). One choice for all slices of a
+// call: the two add in different orders, and a widened last slice shares columns
+// with the one before it.
+bool flat_reduction(const agcn_plan* p, const Slices& first) {
+  return ceil_div64(std::max(p->max_deg, 1), p->H) <= kFlatMaxChunks && first.n * first.L > 16;
+}
+
 template <int VW>
-void launch_hub(const SpmmArgs& a, const Slices& sl) {
+void launch_hub(const SpmmArgs& a, const Slices& sl, bool flat) {
   const agcn_plan* p = a.p;
   const int L = sl.L;
-  // The flat kernel when every hub row has few chunks and the launch covers
-  // more than 16 lanes a row, in slices of 8 or in one (sweep_powerlaw, 7 chunks
-  // at most, per launch: 9.5 against 13.8 us at 8 slices, 6.3 against 7.8 at 4;
-  // at 1 and 2 slices the tree's one workgroup per row was faster, 4.6 against
-  // 5.1 and 5.2 against 5.4).
-  const int64_t max_chunks = ceil_div64(std::max(p->max_deg, 1), p->H);
-  if (max_chunks <= kFlatMaxChunks && sl.n * L > 16) {
+  if (flat) {
+    const int64_t max_chunks = ceil_div64(std::max(p->max_deg, 1), p->H);
     if (max_chunks <= 8) return launch_hub_flat<VW, 8>(a, sl);
     if (max_chunks <= 16) return launch_hub_flat<VW, 16>(a, sl);
     return launch_hub_flat<VW, 32>(a, sl);
@@ -1036,7 +1042,7 @@ int run_phase(const SpmmArgs& a, bool hub_phase, Marks& mk, int sc_max, EntryRan
   Slices sl[2];
   const int n = make_slices<VW>(a.F, sc_max, sl);
   for (int part = 0; part < n; ++part) {
-    if (hub_phase) launch_hub<VW>(a, sl[part]);
+    if (hub_phase) launch_hub<VW>(a, sl[part], flat_reduction(a.p, sl[0]));
     else dispatch_spmm<VW>(a, sl[part], mk, last_range && part == n - 1, er);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, hub_phase ? "k_hub_reduce launch" : "k_spmm launch");

@@ -37,3 +37,22 @@ def test_hub_rows_of_every_unroll_depth(chunks):
     for F in (32, 64, 128, 256):  # 1, 2, 4 and 8 slices
         _spmm_check(p, g, F, seed=F)
     p.destroy()
+
+
+@pytest.mark.parametrize("chunks", [20, 33])
+def test_all_slices_of_a_call_add_in_one_order(chunks):
+    """A last slice of under four columns is widened and shares columns with the
+    one before it: the shared columns are the same bits as without it, whichever
+    kernel reduces (an extra column must not change how the others are added)."""
+    rng = np.random.default_rng(chunks)
+    n, n_cols = 1000, chunks * H + 100
+    deg = rng.integers(0, 40, size=n)
+    deg[rng.choice(n, size=12, replace=False)] = chunks * H
+    g = graphgen.random_csr(n, n_cols, deg, seed=chunks)
+    p = _plan(g)
+    X = torch.randn((n_cols, 160), device="cuda:0")      # rows start on 128-byte lines
+    for F in (64, 96, 128):
+        whole = p.spmm(X[:, :F])
+        for more in (1, 2, 3):
+            assert torch.equal(p.spmm(X[:, :F + more])[:, :F], whole), (F, more)
+    p.destroy()
