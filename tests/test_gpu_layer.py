@@ -52,8 +52,7 @@ def test_linear_matches_oracle(n, fin, fout):
 
 
 def _resident_waves():
-    # Waves the W-resident kernel runs at the widths below: one workgroup of 4
-    # waves per compute unit.
+    # Four waves per compute unit.
     return torch.cuda.get_device_properties(0).multi_processor_count * 4
 
 
@@ -67,11 +66,11 @@ _LAST_ROUND = {"one": lambda w: 1, "eighth": lambda w: w // 8, "eighth+1": lambd
                                                  ("quarter+1", 128, 128, 1), ("quarter+1", 32, 32, 0),
                                                  ("half+1", 128, 128, 2), ("all-3", 64, 128, 9)])
 def test_linear_last_round_split_by_columns(last, fin, fout, short):
-    """16-row tiles past the last whole round of waves are cut by output
-    columns (1, 2, 4 or 8 ranges, depending on how many are left). Every
-    output row stays within the oracle's bound, and is bit-identical to the
-    same row computed inside a whole round: the rows are rotated so that the
-    last round's rows come first and the outputs compared row by row."""
+    """Every output row stays within the oracle's bound and does not depend on
+    its place: the rows are rotated so that the last ones come first and the
+    outputs compared row by row, bit for bit. (These sizes take the bf16-part
+    tiles; the W-resident kernel's last round is tested at fin < 32 in
+    test_gpu_linear_rw.py.)"""
     waves = _resident_waves()
     rem = _LAST_ROUND[last](waves)
     tiles = 2 * waves + rem
@@ -112,10 +111,9 @@ def test_linear_strided_unaligned_and_deterministic():
 
 @pytest.mark.parametrize("offset,pad", [(1, 4), (0, 3), (1, 3)])
 def test_linear_output_rows_not_16_byte_aligned(offset, pad):
-    """fin, fout <= 128 with X and W aligned, but H's rows not all 16-byte
-    aligned (H one float past an aligned address, or a row stride that is not
-    a multiple of 4): the resident-W kernel writes 16-byte pieces, so the
-    tiled kernel runs instead. Within the bound; padding untouched."""
+    """X and W aligned, but H's rows not all 16-byte aligned (H one float past an
+    aligned address, or a row stride that is not a multiple of 4). Within the
+    bound; padding untouched."""
     rng = np.random.default_rng(21 + offset + pad)
     n, fin, fout = 3001, 128, 128
     X = rng.standard_normal((n, fin)).astype(np.float32)
@@ -129,9 +127,9 @@ def test_linear_output_rows_not_16_byte_aligned(offset, pad):
 
 
 def test_linear_wide_output_in_column_launches():
-    """fin <= 128 and fout > 128 run as one W-resident launch per 128 output
-    columns: within the bound, padding columns of a strided H untouched, and
-    each column bit-identical to the same column computed alone."""
+    """More columns than one tile holds: within the bound, padding columns of a
+    strided H untouched, and each column bit-identical to the same column
+    computed in a narrower call."""
     rng = np.random.default_rng(41)
     n, fin, fout = 3001, 96, 260
     X = rng.standard_normal((n, fin)).astype(np.float32)
@@ -291,10 +289,9 @@ def test_layer_captured_in_a_hip_graph_replays_like_eager():
 
 
 def test_linear_padded_strides_and_x_past_4_gib():
-    """The resident-W kernel (fin, fout <= 128, 16-byte aligned rows) with
-    padded leading dimensions: X's padding columns hold infinities that must
-    never be read, H's padding columns stay untouched. X spanning 4 GiB or
-    more takes the tiled kernel: same tolerance."""
+    """Padded leading dimensions: X's padding columns hold infinities that must
+    never be used, H's padding columns stay untouched. Then X spanning 4 GiB or
+    more: same tolerance."""
     rng = np.random.default_rng(11)
     n, fin, fout = 2051, 100, 44
     X = rng.standard_normal((n, fin)).astype(np.float32)
