@@ -30,6 +30,7 @@ from __future__ import annotations
 
 import argparse
 import hashlib
+import math
 import json
 import os
 import sys
@@ -122,11 +123,33 @@ def window_bytes(st, F, hub):
     return b_low, b_hub
 
 
+def slice_cols(st, F, rest_only=False):
+    """Columns per slice of an aggregation of compact rows of F floats from a
+    128-byte aligned X: 32 (one line) where rows start on lines, 64 there on
+    uniform graphs of more columns than the L2s hold lines, and for the rows
+    beside hub windows (rest_only) that gather an X row six times at most; else
+    whole rows up to 256 columns. AGCN_SLICE_COLS overrides."""
+    if F < 4:
+        return F
+    sc = int(os.environ.get("AGCN_SLICE_COLS", "32"))
+    if 4 <= sc <= 256 and sc % 4 == 0 and sc != 32:
+        return min(F, sc)
+    if F % 32 == 0:
+        uniform = st.n_hub_rows == 0 and st.max_deg * st.n_rows <= 8 * st.nnz
+        beside = rest_only and (st.nnz - (st.n_hub_chunks - st.n_hub_rows) * st.hub_chunk_nnz
+                                <= 6 * st.n_cols)
+        return min(F, 64 if (uniform or beside) and st.n_cols > 8 * 32768 and F <= 128 else 32)
+    n = -(-F // 256)
+    return min(F, -(-(-(-F // n)) // 4) * 4)
+
+
 def gather_requests(st, F):
-    """Gather requests one aggregation launch issues for X: every nonzero
-    loads its X row's piece of every column slice of 32 floats (one 128-byte
-    line; a single 64-byte piece when F = 16)."""
-    return st.nnz * ((F + 31) // 32)
+    """128-byte line requests one aggregation launch issues for X: per nonzero
+    and column slice, the lines a piece of a compact row lies on (on average
+    over its possible places where rows do not start on lines)."""
+    sc, g = slice_cols(st, F, windows_used(st, F)), math.gcd(4 * F, 128)
+    lines = lambda cols: 1 + max(0, 4 * cols - g) / 128
+    return int(round(st.nnz * (F // sc * lines(sc) + (lines(F % sc) if F % sc else 0))))
 
 
 def small_path(st):
@@ -136,22 +159,21 @@ def small_path(st):
             and st.n_rows <= 1 << 16)
 
 
-def spmm_kernel_name(F, variant="block", st=None):
-    """Instantiation the library picks for an aligned float32 X: 32-column
-    slices (AGCN_SLICE_COLS overrides), lanes = slice columns / 4."""
+def spmm_kernel_name(F, variant, st):
+    """Instantiation the library picks for compact rows of an aligned float32 X
+    (the first run of column slices): lanes = slice columns / 4, rounded up."""
     if variant == "column_loop":
         return "k_spmm_colloop"
-    if variant == "block" and st is not None and small_path(st):
-        sc = min(F, 32) if F % 4 == 0 else min(F, 64)
-        L = sc // 4 if F % 4 == 0 else sc
-        return f"k_spmm_rows<{4 if F % 4 == 0 else 1}, {L if L in (4, 8) else 0}>"
-    sc = int(os.environ.get("AGCN_SLICE_COLS", "32"))
-    sc = sc if (4 <= sc <= 256 and sc % 4 == 0) else 32
-    sc = min(F, sc)
     if variant == "warp_level":
-        L = sc // 4 if F % 4 == 0 else min(F, sc)
+        sc = int(os.environ.get("AGCN_SLICE_COLS", "32"))
+        sc = min(F, sc if (4 <= sc <= 256 and sc % 4 == 0) else 32)
+        L = sc // 4 if F % 4 == 0 else min(sc, 64)
         return f"k_spmm_wl<{4 if F % 4 == 0 else 1}, {L if L in (4, 8) else 0}>"
-    return f"k_spmm<4, {sc // 4}>" if F % 4 == 0 else f"k_spmm<1, {min(F, sc, 64)}>"
+    sc, vw = slice_cols(st, F, windows_used(st, F)), 4 if F >= 4 else 1
+    L = -(-sc // vw)
+    if small_path(st):
+        return f"k_spmm_rows<{vw}, {L if L in (4, 8) else 0}>"
+    return f"k_spmm<{vw}, {L if L in ((1, 2, 4, 8, 16, 32, 64) if vw == 4 else (1, 2)) else 0}>"
 
 
 def source_hash(path=KERNEL_SRC):
@@ -321,17 +343,6 @@ MFMA_FP32_PEAK_TFLOPS = 157.3
 MFMA_SPLIT_PEAK_TFLOPS = 2500.0 / 8
 
 
-def linear_kernel_name(fin, fout):
-    """Name by which records made with the fp32 linear kernels (k_linear_rw with
-    W resident, the tiled k_linear) list a shape; linear_kernel names today's."""
-    vec = fin % 4 == 0 and fout % 4 == 0
-    if vec and 1 <= fin <= 128 and fout <= 128:
-        nb = 2 if fout <= 32 else 4 if fout <= 64 else 8
-        ks = 2 if fin <= 32 else 4 if fin <= 64 else 8
-        return f"k_linear_rw<{nb}, {ks}>"
-    return f"k_linear<{32 if fout <= 32 else 64 if fout <= 64 else 128}, {'true' if vec else 'false'}>"
-
-
 def linear_kernel(n, fin, fout):
     """Kernel agcn_linear picks for compact, 16-byte aligned float32 matrices."""
     cdiv = lambda a, b: -(-a // b)
@@ -342,6 +353,24 @@ def linear_kernel(n, fin, fout):
     if fout > 32 and cdiv(n, 128) * cdiv(fout, 64) < 512 and fin <= 256:
         return "k_linear_split<4, 4>"
     return f"k_linear_split<{8 if fout > 64 else cdiv(fout, 16)}, 8>"
+
+
+def gather_cost(F):
+    """agcn_gcn_layer's price of one aggregation per nonzero, compact rows."""
+    g = math.gcd(4 * F, 128)
+    if g == 128:
+        return 0.85 if F <= 16 else float(-(-F // 32))
+    lines = 1.0 + max(0.0, (4.0 * F - g) / 128.0)
+    if lines <= 1.0:
+        return 0.85 if F <= 16 else 1.0
+    return 1.25 * lines if lines > 2.5 else lines
+
+
+def aggregates_first(st, fin, fout):
+    """Whether agcn_gcn_layer runs (A X) W (compact, aligned matrices; the
+    workspace of a square graph without many more hub chunks than rows)."""
+    return (st.flags == 0 and 1 <= fin < fout and 0 < st.n_rows <= st.n_cols and st.nnz > 0
+            and st.hub_windows == 0 and gather_cost(fin) <= 0.85 * gather_cost(fout))
 
 
 def bench_layer(args):
@@ -373,7 +402,6 @@ def bench_layer(args):
     st = agcn.agcn_plan_info(plan)
     nb = agcn.agcn_gcn_workspace_size(plan, fout)
     ws = torch.empty((nb + 3) // 4, dtype=torch.float32, device=dev)
-    H = ws[: g.n_cols * fout].view(g.n_cols, fout)
     relu = agcn.AGCN_EPILOGUE_RELU
 
     def layer():
@@ -391,40 +419,59 @@ def bench_layer(args):
     torch.cuda.synchronize()
     ms_step = e0.elapsed_time(e1) / args.steps
     log(f"timed {args.steps} layer steps: {ms_step:.4f} ms/step")
-    # The two halves of the same call, timed on their own for the roofline:
-    # agcn_linear into the same workspace, then the aggregation with ReLU.
+    # The two halves of the same call, timed on their own for the roofline, in the
+    # order that the call takes: A (X W), or (A X) W with A X in the workspace.
+    first = aggregates_first(st, fin, fout)
+    F_agg = fin if first else fout
+    n_lin = g.n_rows if first else g.n_cols
+    part = agcn.agcn_spmm_workspace_size(plan, F_agg)
+    T = torch.empty((n_lin, F_agg), dtype=torch.float32, device=dev)
+    pws = torch.empty(part // 4 + 1, dtype=torch.float32, device=dev)
+
+    def linear_half(src, dst):
+        agcn.agcn_linear(n_lin, fin, fout, src.data_ptr(), fin, W.data_ptr(), fout, dst.data_ptr(),
+                         fout, sh)
+
+    def aggregation_half(src, dst, act):
+        agcn.agcn_spmm_ex(plan, F_agg, src.data_ptr(), F_agg, dst.data_ptr(), F_agg,
+                          pws.data_ptr() if part else None, sh, act)
+
     marks = [(ev(), ev(), ev()) for _ in range(args.steps)]
     for a, b, c in marks:
         a.record(stream)
-        agcn.agcn_linear(g.n_cols, fin, fout, X.data_ptr(), fin, W.data_ptr(), fout, H.data_ptr(),
-                         fout, sh)
+        if first:
+            aggregation_half(X, T, 0)
+        else:
+            linear_half(X, T)
         b.record(stream)
-        agcn.agcn_spmm_ex(plan, fout, H.data_ptr(), fout, Y.data_ptr(), fout,
-                          ws[(nb - agcn.agcn_spmm_workspace_size(plan, fout)) // 4:].data_ptr()
-                          if agcn.agcn_spmm_workspace_size(plan, fout) else None, sh, relu)
+        if first:
+            linear_half(T, Y)
+        else:
+            aggregation_half(T, Y, relu)
         c.record(stream)
     torch.cuda.synchronize()
-    lin_ms = float(np.mean([a.elapsed_time(b) for a, b, _ in marks]))
-    agg_ms = float(np.mean([b.elapsed_time(c) for _, b, c in marks]))
+    halves = [float(np.mean([m[k].elapsed_time(m[k + 1]) for m in marks])) for k in (0, 1)]
+    agg_ms, lin_ms = halves if first else halves[::-1]
     agcn.agcn_plan_destroy(plan)
-    fl_lin = 2.0 * g.n_cols * fin * fout
-    fl_agg = 2.0 * g.nnz * fout
+    fl_lin = 2.0 * n_lin * fin * fout
+    fl_agg = 2.0 * g.nnz * F_agg
     ach = fl_lin / (lin_ms * 1e-3) / 1e12
-    kname = linear_kernel(g.n_cols, fin, fout)
+    kname = linear_kernel(n_lin, fin, fout)
     peak = MFMA_FP32_PEAK_TFLOPS if "_rw" in kname else MFMA_SPLIT_PEAK_TFLOPS
-    lin_bytes = int(4 * g.n_cols * (fin + fout) + 4 * fin * fout)
+    lin_bytes = int(4 * n_lin * (fin + fout) + 4 * fin * fout)
     if lin_bytes / (HBM_PEAK_GBPS * 1e9) > fl_lin / (peak * 1e12):
         bound, unit, ach, peak = "hbm", "GB/s", lin_bytes / (lin_ms * 1e-3) / 1e9, HBM_PEAK_GBPS
     else:
         bound, unit = "mfma", "TFLOP/s"
     out = {
-        "metric": "GCNConv layer forward GFLOP/s (2·N·fin·fout + 2·nnz·fout)",
+        "metric": "GCNConv layer forward GFLOP/s (2·N·fin·fout + 2·nnz·F, F the width aggregated at)",
         "value": round((fl_lin + fl_agg) / (ms_step * 1e-3) / 1e9, 3), "unit": "GFLOP/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_step, 5),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": name, "n_rows": g.n_rows, "nnz": g.nnz, "fin": fin, "fout": fout,
-                   "activation": "relu", "parallelism": "single GPU"},
+                   "activation": "relu", "parallelism": "single GPU",
+                   "order": "(A X) W" if first else "A (X W)"},
         "plan_ms_once": round(plan_ms, 4), "linear_ms": round(lin_ms, 5),
         "aggregation_ms": round(agg_ms, 5),
         "roofline": {"bound": bound, "achieved": round(ach, 2), "peak": round(peak, 1),

@@ -36,40 +36,78 @@ def test_kernel_bytes_model(F):
     assert w8 == 8 * st.n_rows
 
 
-def test_kernel_names_match_the_library_dispatch():
-    assert bench.spmm_kernel_name(16) == "k_spmm<4, 4>"
-    assert bench.spmm_kernel_name(256) == "k_spmm<4, 8>"
-    assert bench.spmm_kernel_name(17) == "k_spmm<1, 17>"
-    assert bench.spmm_kernel_name(64, "column_loop") == "k_spmm_colloop"
-    assert bench.spmm_kernel_name(64, "warp_level") == "k_spmm_wl<4, 8>"
+class _Graph:
+    """A power-law plan of the default workload's size."""
+    n_rows = n_cols = 230_000
+    nnz, n_hub_rows, max_deg, max_wave_nzs = 11_386_022, 4_000, 3_391, 32
+    n_hub_chunks, hub_chunk_nnz, hub_windows, flags = 9_000, 512, 0, 0
 
 
-def test_linear_kernel_names_match_the_library_dispatch():
-    assert bench.linear_kernel_name(128, 128) == "k_linear_rw<8, 8>"
-    assert bench.linear_kernel_name(32, 16) == "k_linear_rw<2, 2>"
-    assert bench.linear_kernel_name(64, 100) == "k_linear_rw<8, 4>"
-    assert bench.linear_kernel_name(256, 128) == "k_linear<128, true>"
-    assert bench.linear_kernel_name(128, 200) == "k_linear<128, true>"
-    assert bench.linear_kernel_name(30, 64) == "k_linear<64, false>"
+class _Uniform(_Graph):
+    n_rows = n_cols = 1_000_000
+    nnz, n_hub_rows, max_deg, n_hub_chunks = 20_000_000, 0, 50, 0
+
+
+@pytest.mark.parametrize("st,F,cols,name", [
+    (_Graph, 16, 16, "k_spmm<4, 4>"), (_Graph, 32, 32, "k_spmm<4, 8>"), (_Graph, 256, 32, "k_spmm<4, 8>"),
+    (_Graph, 17, 17, "k_spmm<4, 0>"), (_Graph, 40, 40, "k_spmm<4, 0>"), (_Graph, 64, 32, "k_spmm<4, 8>"),
+    (_Graph, 100, 100, "k_spmm<4, 0>"), (_Graph, 300, 152, "k_spmm<4, 0>"), (_Graph, 3, 3, "k_spmm<1, 0>"),
+    (_Graph, 2, 2, "k_spmm<1, 2>"), (_Graph, 500, 252, "k_spmm<4, 0>"), (_Uniform, 64, 64, "k_spmm<4, 16>"),
+    (_Uniform, 128, 64, "k_spmm<4, 16>"), (_Uniform, 256, 32, "k_spmm<4, 8>")])
+def test_kernel_names_match_the_library_dispatch(st, F, cols, name):
+    assert bench.slice_cols(st, F) == cols
+    assert bench.spmm_kernel_name(F, "block", st) == name
+
+
+def test_ablation_kernel_names():
+    assert bench.spmm_kernel_name(64, "column_loop", _Graph) == "k_spmm_colloop"
+    assert bench.spmm_kernel_name(64, "warp_level", _Graph) == "k_spmm_wl<4, 8>"
+
+
+@pytest.mark.parametrize("n,fin,fout,name", [
+    (230_000, 28, 128, "k_linear_rw<8>"), (230_000, 16, 32, "k_linear_rw<2>"), (230_000, 16, 60, "k_linear_rw<4>"),
+    (230_000, 32, 16, "k_linear_split<1, 8>"), (230_000, 33, 17, "k_linear_split<2, 8>"),
+    (230_000, 256, 40, "k_linear_split<3, 8>"), (230_000, 128, 64, "k_linear_split<4, 8>"),
+    (230_000, 602, 256, "k_linear_split<8, 8>"), (30_000, 64, 64, "k_linear_split<4, 4>"),
+    (3_000, 1000, 16, "k_linear_ksplit<1, 8>"), (12_000, 128, 64, "k_linear_ksplit<4, 4>")])
+def test_linear_kernel_names_match_the_library_dispatch(n, fin, fout, name):
+    assert bench.linear_kernel(n, fin, fout) == name
+    # the tile shapes named are those the library's source launches
+    src = open(os.path.join(ROOT, "paper_2308_11825_amd", "csrc", "agcn_linear.hip")).read()
+    kind, args = name.split("<")
+    launch = {"k_linear_rw": "launch_rw", "k_linear_split": "launch_split", "k_linear_ksplit": "launch_ksplit"}
+    assert f"{launch[kind]}<{args}(" in src
+
+
+def test_layer_order_matches_the_library():
+    assert bench.aggregates_first(_Graph, 128, 256) and bench.aggregates_first(_Graph, 16, 32)
+    assert not bench.aggregates_first(_Graph, 100, 128)
+    assert not bench.aggregates_first(_Graph, 128, 128) and not bench.aggregates_first(_Graph, 256, 40)
+    class Win(_Graph):
+        hub_windows = 100
+    assert not bench.aggregates_first(Win, 128, 256)
 
 
 def test_small_path_kernel_name():
-    class St:
-        n_hub_rows, max_deg, max_wave_nzs, nnz, n_rows = 0, 21, 32, 36844, 4096
+    class St(_Graph):
+        n_hub_rows, max_deg, max_wave_nzs, nnz, n_rows, n_cols = 0, 21, 32, 36844, 4096, 4096
     assert bench.small_path(St)
     assert bench.spmm_kernel_name(16, "block", St) == "k_spmm_rows<4, 4>"
     assert bench.spmm_kernel_name(64, "block", St) == "k_spmm_rows<4, 8>"
+    assert bench.spmm_kernel_name(17, "block", St) == "k_spmm_rows<4, 0>"
     St.max_deg = 33
     assert not bench.small_path(St)
     assert bench.spmm_kernel_name(16, "block", St) == "k_spmm<4, 4>"
 
 
 def test_gather_requests_model():
-    class St:
+    class St(_Graph):
         nnz = 1000
     assert bench.gather_requests(St, 16) == 1000
     assert bench.gather_requests(St, 32) == 1000
     assert bench.gather_requests(St, 256) == 8000
+    assert bench.gather_requests(St, 40) == 2000        # 160 bytes from any multiple of 32
+    assert bench.gather_requests(St, 41) == 1000 + 1250  # 164 bytes from any multiple of 4
 
 
 class _WinStats:
