@@ -68,11 +68,13 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 // A wave takes 16 rows: with 32 the two accumulators leave 3 waves per SIMD or
 // fewer (1e6 x 64 -> 64 120 us against 109, 64 -> 128 128 against 95, 230,000 x
 // 602 -> 64 184 against 167; with 256 columns a tile spills).
-// Bound (230,000 rows): matrix cores from fin 256 up, memory below. Measured with
-// the fp32 matrix instruction and now: 602 -> 256 797 -> 504 us (1.14 PFLOP/s of
-// bf16 products, what a library's bf16 product of 8192^3 reaches on this card is
-// 1.16), 512 -> 128 280 -> 231, 128 -> 128 71 -> 62, 128 -> 64 41 -> 39, 33 -> 17
-// 22 -> 16; 170,000 x 256 -> 40 63 -> 41; 1e6 x 64 -> 64 101 -> 109.
+// Bound: matrix cores from fin 256 up, memory below. Measured with the fp32 matrix
+// instruction and now, us: 230,000 rows 602 -> 256 797 and 500 (1.15 PFLOP/s of bf16
+// products, what a library's bf16 product of 8192^3 reaches on this card is 1.16),
+// 512 -> 128 280 and 231, 128 -> 128 70 and 69, 128 -> 64 41 and 44, 33 -> 17 22 and
+// 19; 170,000 x 256 -> 40 63 and 44; 1e6 rows 100 -> 100 283 and 277, 64 -> 64 101
+// and 119, 64 -> 16 58 and 67. (Six products in one sum, which lost bits: 395, 191,
+// 56, 35, 17; 38; 235, 101, 60.)
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
@@ -287,7 +289,7 @@ template <int NB>
 __device__ inline void sp_redo(uint32_t bad, const float* __restrict__ xr, int i, int g, int col0,
                                int32_t fin, int32_t fout, const float* __restrict__ W, int64_t ldw,
                                float* __restrict__ Hrow, int32_t act) {
-  constexpr int GB = NB % 2 == 0 ? 2 : 1;
+  constexpr int GB = NB == 8 ? 2 : 1;
   static_assert(NB % GB == 0, "");
 #pragma unroll 1
   for (int b0 = 0; b0 < NB; b0 += GB, bad >>= GB) {
@@ -352,10 +354,12 @@ __device__ inline void sp_store(const f4* acc, const float* __restrict__ xr, int
     sp_redo<NB>(bad, xr, i, g, col0, fin, fout, W, ldw, Hrow, act);
 }
 
-// (The second launch bound keeps the registers of the rare sp_redo from costing a
-// wave per SIMD: 602 -> 256 566 us without it.)
+// (The second launch bound keeps the registers of the rare sp_redo from costing
+// waves: 230,000 x 602 -> 256 566 us without it, 170,000 x 256 -> 40 47.5 with 4
+// for 48 columns and 44.5 with 6. One column block at a time in sp_redo for the
+// narrower tiles, for the same reason.)
 template <int NB, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, NB <= 2 ? 6 : 4) void k_linear_split(
+__global__ __launch_bounds__(WAVES * 64, NB <= 3 ? 6 : NB == 4 ? 5 : 4) void k_linear_split(
     int64_t n, int32_t fin, int32_t fout, int32_t n_ct, const float* __restrict__ X, int64_t ldx,
     const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
   constexpr int T = WAVES * 64, BM = WAVES * 16;
@@ -410,12 +414,13 @@ __global__ __launch_bounds__(WAVES * 64, NB <= 2 ? 6 : 4) void k_linear_split(
 }
 
 // k_linear_ksplit: few rows leave k_linear_split a handful of workgroups that
-// walk the chunks in series (3000 x 1000 -> 16: 24 us, a load latency per
+// walk the chunks in series (3000 x 1000 -> 16: 26 us, a load latency per
 // chunk). Here a workgroup takes 16 rows and NB * 16 columns, its waves take the
 // chunks in turn (each loads and cuts its own W fragments from L2), and wave 0
-// adds the waves' sums in wave order: 5.4 us.
+// adds the waves' sums in wave order: 5.9 us. (The second launch bound as in
+// k_linear_split: 16,000 x 256 -> 64 13.6 us without it, 11.3 with.)
 template <int NB, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
+__global__ __launch_bounds__(WAVES * 64, 4) void k_linear_ksplit(
     int64_t n, int32_t fin, int32_t fout, const float* __restrict__ X, int64_t ldx,
     const float* __restrict__ W, int64_t ldw, float* __restrict__ H, int64_t ldh, int32_t act) {
   __shared__ f4 part[WAVES][2][NB][64];  // the waves' hi and lo sums
@@ -462,7 +467,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
   if (lane == 0) s_tiny[wave] = mine;
   __syncthreads();
   if (wave != 0) return;
-  constexpr int kAhead = NB == 4 ? 3 : WAVES;  // (all of them at once spill with 64 columns)
+  constexpr int kAhead = NB == 4 ? 1 : NB == 2 ? 3 : WAVES;  // (more at once cost registers)
 #pragma unroll kAhead
   for (int w = 1; w < WAVES; ++w)
 #pragma unroll
@@ -510,8 +515,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_linear_ksplit(
 //      takes element t, paired with W^T[col][16 s + 4 g + t] from one 16-byte
 //      LDS read; the four instructions together cover k = 16 s .. 16 s + 15.
 // fp32 products, bound by memory at these sizes. Against k_linear_split, whose
-// only chunk is then partly empty: 230,000 rows 12 -> 128 25.9 and 27.3 us, 16 ->
-// 64 15.9 and 16.0; 2.4 M rows 8 -> 8 47.0 and 51.7, 16 -> 32 107.6 and 108.9.
+// only chunk is then partly empty: 230,000 rows 12 -> 128 28.9 and 30.5 us, 16 ->
+// 64 16.9 and 19.9; 2.4 M rows 8 -> 8 47.6 and 72.8, 16 -> 32 109 and 126.
 constexpr int kRwThreads = 256;
 constexpr int kRwWaves = kRwThreads / 64;
 constexpr int kRwRows = 16;
@@ -734,9 +739,10 @@ int run_linear(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx
     return AGCN_OK;
   }
   // Few (16 rows, 64 columns) tiles and more than one chunk: the k split.
-  // 3000 x 1000 -> 16 / 64 / 256: 5.4 / 10.2 / 23.5 us against 24.9 / 25.6 / 29.3;
-  // 12,000 x 128 -> 64 5.4 against 6.1. Past the line it repeats the W cuts too
-  // often: 12,000 x 128 -> 256 13.4 against 10.0, 30,000 x 500 -> 40 33 against 22.
+  // 3000 x 1000 -> 16 / 64 / 256 5.9 / 11.5 / 26 us against 26 / 40 / 63 in tiles,
+  // 12,000 x 128 -> 64 6.6 against 7.2, 16,000 x 256 -> 64 10.6 against 12.0. Past
+  // the line it repeats the W cuts too often: 12,000 x 128 -> 256 16.6 against 12.3,
+  // 25,000 x 64 -> 64 9.9 against 6.7, 30,000 x 500 -> 40 38 against 23.
   if (fin > 32 && ceil_div64(n, 16) * ceil_div64(fout, 64) <= 2 * kFewGroups) {
     const bool many = fin > 256;
     if (fout <= 16)
@@ -748,8 +754,8 @@ int run_linear(int64_t n, int32_t fin, int32_t fout, const float* X, int64_t ldx
     return many ? launch_ksplit<4, 8>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act)
                 : launch_ksplit<4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
   }
-  // 64 rows by 64 columns where 128-row tiles are few: 12,000 x 16 -> 128 4.7
-  // against 5.0 us, 30,000 x 64 -> 64 5.6 against 6.4.
+  // 64 rows by 64 columns where 128-row tiles are few: 20,000 x 64 -> 100 7.9 us
+  // against 8.6, 40,000 x 128 -> 64 12.0 against 12.8.
   if (fout > 32 && ceil_div64(n, 128) * ceil_div64(fout, 64) < kFewGroups && fin <= 256)
     return launch_split<4, 4>(n, fin, fout, X, ldx, W, ldw, H, ldh, st, act);
   // The narrowest tile that holds fout (a wider one multiplies padding): 170,000 x
