@@ -562,12 +562,12 @@ int linear_checked(int64_t n, int32_t fin, int32_t fout, const float* d_X, int64
 // of fout. The gathers of the aggregation are what a layer spends its time on,
 // so where they cost clearly less at fin (170,000 rows, mean degree 14, 128 ->
 // 256: aggregation 206 -> 101 us, layer 287 -> 184 us, the linear step's work
-// being the same). Not for the ablation baselines; not where the hub rows run
-// over column windows at fout (F >= 64), which costs less than hub chunks at a
-// smaller fin (1000 hub rows of 1e5 nonzeros: F = 32 920 us, F = 64 817); not
-// where A X has more rows than X W; and only if the workspace, sized for X W,
-// holds A X (T) and its hub partials. Arguments that the calls of the other
-// order refuse go that way.
+// being the same). Not for the ablation baselines; not for plans with hub-row
+// windows: at fin < 64 A X would take hub chunks, which cost more than the
+// windows at fout (1000 hub rows of 1e5 nonzeros: F = 32 920 us, F = 64 817; widths
+// that both take the windows were not compared); not where A X has more rows than
+// X W; and only if the workspace, sized for X W, holds A X (T) and its hub
+// partials. Arguments that the calls of the other order refuse go that way.
 bool aggregate_first(agcn_plan_t plan, int32_t fin, int32_t fout, const float* X, int64_t ldx,
                      const float* W, int64_t ldw, const float* Y, int64_t ldy, const float* ws,
                      size_t ws_bytes, size_t* t_bytes) {
